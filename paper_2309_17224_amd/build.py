@@ -14,7 +14,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libfp8lin.so")
-SOURCES = ["fp8lin_api.hip", "fp8lin_amax_cast.hip", "fp8lin_gemm.hip", "fp8lin_decoder.hip"]
+SOURCES = ["fp8lin_api.hip", "fp8lin_amax_cast.hip", "fp8lin_gemm.hip", "fp8lin_gemm_ragged.hip", "fp8lin_decoder.hip"]
 # measurement aid beside the library (bench.py --mfma-ceiling), not the method
 PROBE_LIB = os.path.join(PKG, "libfp8probe.so")
 PROBE_SOURCE = "fp8probe.hip"
@@ -49,7 +49,7 @@ def build(verbose: bool = False, jobs: int | None = None) -> str:
     if verbose:
         for cmd in cmds:
             print(" ".join(cmd), flush=True)
-    jobs = jobs or min(len(cmds), max(1, (os.cpu_count() or 1) // 2))
+    jobs = jobs or min(len(cmds), max(1, os.cpu_count() or 1))
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         for r in ex.map(lambda c: subprocess.run(c, check=True), cmds):
             pass

@@ -43,171 +43,18 @@
 //    groups of 8 tile-rows, so tiles sharing operand panels meet in the same
 //    L2.
 // Decode kernel (M <= 32): weight-streaming split-K, see below.
-// Fallback kernel (K not a multiple of 128, or K >= 2^22): 64 x 64 tiles,
-// 16-byte loads when K is a multiple of 16 and byte loads otherwise, with
-// bounds checks and zero fill, same MFMA and epilogue.
-#include "fp8lin_fp8.h"
-#include "fp8lin_internal.h"
+// K not a multiple of 128, or K >= 2^22: fp8lin_gemm_ragged.hip.
+#include "fp8lin_mm.h"
 
 namespace fp8lin {
 namespace {
 
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-// MFMA operand format selectors: 0 = fp8 (E4M3), 1 = bf8 (E5M2).
-template <int F0, int F1>
-__device__ __forceinline__ v4f mfma16(v8i a, v8i b, v4f c) {
-    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, F0, F1, 0, 0, 0, 0);
-}
-
-__device__ __forceinline__ uint32_t f32_to_bf16_rne(float f) {
-    const uint32_t u = __float_as_uint(f);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return 0x7FC0u;
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, off, 64));
-    return v;
-}
-
-// 32-bit LDS address of a pointer into a __shared__ array.
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
-}
-
-// Wait until at most N vector-memory operations of this wave are in flight.
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-    static_assert(N >= 0 && N < 64, "vmcnt range");
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
-}
-
-// Wait until every LDS read of this wave has returned its data.
-__device__ __forceinline__ void wait_lgkmcnt0() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
-
-// Workgroup barrier with no memory fence: the main loop orders its LDS
-// traffic itself (wait_vmcnt for the copies, wait_lgkmcnt0 for the reads).
-__device__ __forceinline__ void ws_barrier() {
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-}
-
-// The two 16-byte pieces of an MFMA operand fragment, as one 8-register vector.
-__device__ __forceinline__ v8i ld_frag(const uint8_t* p, int fo0, int fo1) {
-    const uint4 p0 = *(const uint4*)(p + fo0);
-    const uint4 p1 = *(const uint4*)(p + fo1);
-    return v8i{(int)p0.x, (int)p0.y, (int)p0.z, (int)p0.w, (int)p1.x, (int)p1.y, (int)p1.z, (int)p1.w};
-}
-
-// Physical 16-byte chunk of logical chunk c in LDS operand row r is
-// c ^ chunk_swz(r).  A fragment read has lane l on row r = l % 16 (row bit 0
-// picks the half of a 256-byte bank line) and logical chunk 2 (l / 16) + piece.
-// Within one phase (fixed lane bit 5 and parity of lane bits 2..4) the map
-// (r1, r2, r3) -> (r1 ^ piece, parity ^ r3, bit 5 ^ r2) of the three chunk bits
-// is one-to-one, so the 16 lanes hit 16 distinct bank groups.
-__device__ __forceinline__ int chunk_swz(int r) { return ((r >> 1) & 1) | (((r >> 2) & 1) << 2); }
-
-// Contiguous tile ranges per XCD, then grouped row-major order inside.
-__device__ __forceinline__ void tile_of(int b, int nb, int tiles_m, int tiles_n, int& tm, int& tn) {
-    const int x = b & 7, l = b >> 3;
-    const int per = nb >> 3, rem = nb & 7;
-    const int t = x * per + min(x, rem) + l;
-    constexpr int G = 8;
-    const int group = G * tiles_n;
-    const int gid = t / group;
-    const int first = gid * G;
-    const int gm = min(tiles_m - first, G);
-    const int r = t - gid * group;
-    tm = first + r % gm;
-    tn = r / gm;
-}
-
-// Store 4 consecutive outputs of row m starting at column n (unscaled by
-// 2^-sh); returns the largest output magnitude pattern (as fp32 bits).
-template <int OUT_DT>
-__device__ __forceinline__ uint32_t store4(void* C, int64_t ldc, int64_t m, int64_t n, int64_t M,
-                                           int64_t N, v4f acc, int sh, bool vec) {
-    float y[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) y[v] = ldexpf(acc[v], sh);
-    uint32_t mx = 0;
-    if (OUT_DT == FP8_DT_BF16) {
-        uint32_t h[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            h[v] = f32_to_bf16_rne(y[v]);
-            mx = max(mx, (h[v] & 0x7FFFu) << 16);
-        }
-        if (m < M) {
-            uint16_t* p = (uint16_t*)C + m * ldc + n;
-            if (vec && n + 3 < N) {
-                *(uint2*)p = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-            } else {
-                for (int v = 0; v < 4; ++v)
-                    if (n + v < N) p[v] = (uint16_t)h[v];
-            }
-        }
-    } else {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) mx = max(mx, __float_as_uint(y[v]) & 0x7FFFFFFFu);
-        if (m < M) {
-            float* p = (float*)C + m * ldc + n;
-            if (vec && n + 3 < N) {
-                *(float4*)p = make_float4(y[0], y[1], y[2], y[3]);
-            } else {
-                for (int v = 0; v < 4; ++v)
-                    if (n + v < N) p[v] = y[v];
-            }
-        }
-    }
-    return m < M ? mx : 0u;
-}
-
-// Unscale exponent of output row m (of M): -(ba + bb), with ba of row m when
-// ba_rows (per-row activation biases, one per data sample or segment).
-__device__ __forceinline__ int row_shift(const int32_t* ba_p, int ba_rows, int bb, int64_t m, int64_t M) {
-    return -((ba_rows ? ba_p[min(m, M - 1)] : ba_p[0]) + bb);
-}
-
 // ------------------------------------------------------------ main kernel
-constexpr int kBM = 256, kBN = 256, kBK = 128, kThreads = 256;
+constexpr int kBM = 256, kBN = 256, kBK = 128;
 constexpr int kMainThreads = 512;      // 8 waves: two groups of four
 constexpr int kTileBytes = kBM * kBK;  // one operand tile, 32 KiB
 
-// Direct L2 -> LDS copy of 16 bytes per lane (global_load_lds_dwordx4, the
-// form with a wave-uniform 64-bit base in SGPRs and a 32-bit lane offset):
-// lane i's 16 bytes land at lds_row + 16 i; lds_row must be wave-uniform.
-// The instruction is issued from inline assembly so that the compiler does
-// not treat every later LDS read as dependent on it (it cannot tell the two
-// halves of the double buffer apart and would wait for the prefetch before
-// each read); completion is tracked with wait_vmcnt.
-__device__ __forceinline__ void lds_dma16_s(const uint8_t* sbase, uint32_t voff, uint32_t lds_row) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(lds_row), "v"(voff), "s"(sbase)
-                 : "memory");
-}
-
-// The same copy with the non-temporal hint (a stream read once).
-__device__ __forceinline__ void lds_dma16_nt(const uint8_t* sbase, uint32_t voff, uint32_t lds_row) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
-                 :
-                 : "s"(lds_row), "v"(voff), "s"(sbase)
-                 : "memory");
-}
-
 __device__ __forceinline__ int bq_used(const int32_t* pred) { return clamp_bias(*pred); }
-
-// 16-byte store of matmul output with the non-temporal hint: the output is not
-// read again by this kernel and should not displace cached operands.
-__device__ __forceinline__ void st_stream(void* p, uint4 v) {
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, (u32x4*)p);
-}
 
 // Epilogue staging rows (bytes): 32 output rows of a wave per pass; the
 // codes of the fused quantise (256 x 256 bytes) follow the bf16 staging area.
@@ -235,29 +82,7 @@ struct QuantOut {
     int64_t ldy8;
     uint8_t* y8t;  // may be null
     int64_t ldy8t;
-    int vec8, vec8t;  // 16-byte stores allowed
 };
-
-// Eq. 3 bias of the output taken in the same launch (ws != nullptr): every
-// workgroup folds its largest |Y| pattern into ws[0] and then counts itself
-// in ws[1]; the last one to count takes the total, writes amax, bias and
-// flags, and leaves both words zero for the next call.
-struct BiasOut {
-    int32_t* bias;
-    uint32_t* flags;  // may be null
-    uint32_t* ws;     // [0] running maximum, [1] finished workgroups; zero between calls
-    int fmt;
-    int32_t margin;
-};
-
-__device__ __forceinline__ int32_t bias_of_fmt(int fmt, uint32_t a, int32_t margin, uint32_t* fl) {
-    switch (fmt) {
-        case FP8_E4M3: return bias_of<FP8_E4M3>(a, margin, fl);
-        case FP8_E5M2: return bias_of<FP8_E5M2>(a, margin, fl);
-        case FP8_E4_A: return bias_of<FP8_E4_A>(a, margin, fl);
-        default: return bias_of<FP8_E5_A>(a, margin, fl);
-    }
-}
 
 // One output tile of 256 rows x TN columns (TN = 64..256; each wave owns 64
 // rows x TN/2 columns), tile number bid of nb in this workgroup's share of the
@@ -267,7 +92,7 @@ template <int FA, int FB, int OUT_DT, bool AMAX, int QF, int TN>
 __device__ __forceinline__ void gemm_tile(
     uint8_t* __restrict__ smem, int bid, int nb, const uint8_t* __restrict__ A, const uint8_t* __restrict__ B,
     const int32_t* __restrict__ ba_p, const int32_t* __restrict__ bb_p, void* __restrict__ C, int M, int N, int K,
-    int tiles_m, int tiles_n, int col0, int vec_out, uint32_t* __restrict__ amax_out, const QuantOut& qo,
+    int tiles_m, int tiles_n, int col0, uint32_t* __restrict__ amax_out, const QuantOut& qo,
     const BiasOut& bo, int ba_rows) {
     static_assert(QF < 0 || OUT_DT == FP8_DT_BF16, "fused quantise is for bf16 outputs");
     static_assert(QF < 0 || TN == 256, "fused quantise stages whole 256 x 256 tiles");
@@ -480,7 +305,7 @@ __device__ __forceinline__ void gemm_tile(
                 const int64_t m = m0 + wr0 + i2 * 32 + row, n = n0 + wc0 + c16 * 8;
                 if (m < M && c16 < TN / 16) {
                     uint16_t* p = (uint16_t*)C + m * N + n;
-                    if (vec_out && n + 8 <= N) {
+                    if (n + 8 <= N) {
                         st_stream(p, v);
                     } else {
                         const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
@@ -500,8 +325,8 @@ __device__ __forceinline__ void gemm_tile(
                 const int64_t m = m0 + r, n = n0 + c * 16;
                 if (m < M && n < N) {
                     uint8_t* p = qo.y8 + m * qo.ldy8 + n;
-                    if (qo.vec8 && n + 16 <= N) {
-                        *(uint4*)p = v;
+                    if (n + 16 <= N) {
+                        st16_any(p, v);
                     } else {
                         const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
                         for (int e = 0; e < 16 && n + e < N; ++e) p[e] = (uint8_t)(wv[e >> 2] >> (8 * (e & 3)));
@@ -531,8 +356,8 @@ __device__ __forceinline__ void gemm_tile(
                     const int64_t n = n0 + c, m = m0 + q * 16;
                     if (n < N && m < M) {
                         uint8_t* p = qo.y8t + n * qo.ldy8t + m;
-                        if (qo.vec8t && m + 16 <= M) {
-                            *(uint4*)p = v;
+                        if (m + 16 <= M) {
+                            st16_any(p, v);
                         } else {
                             const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
                             for (int e = 0; e < 16 && m + e < M; ++e) p[e] = (uint8_t)(wv[e >> 2] >> (8 * (e & 3)));
@@ -567,7 +392,7 @@ __device__ __forceinline__ void gemm_tile(
                 const int64_t m = m0 + wr0 + i2 * 32 + row, n = n0 + wc0 + c32 * 4;
                 if (m < M && c32 < TN / 8) {
                     float* p = (float*)C + m * N + n;
-                    if (vec_out && n + 4 <= N) {
+                    if (n + 4 <= N) {
                         st_stream(p, make_uint4(__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)));
                     } else {
                         const float fv[4] = {v.x, v.y, v.z, v.w};
@@ -591,30 +416,7 @@ __device__ __forceinline__ void gemm_tile(
             uint32_t b = 0;
 #pragma unroll
             for (int v = 0; v < kMainThreads / 64; ++v) b = max(b, wmx[v]);
-            const uint32_t bc = canon_amax(b);  // the fold and the atomics take canonical NaNs
-            if (AMAX && !bo.ws) atomicMax(amax_out, bc);
-            if (AMAX && bo.ws) {
-                // The fold is a returning device-scope atomic whose result is
-                // consumed by an asm statement that also clobbers memory: the
-                // compiler cannot move the count above it, and the hardware
-                // has performed the fold (the wait for its return) before the
-                // count is issued.  The workgroup that counts last therefore
-                // finds every fold in ws[0].  A release/acquire count would
-                // say the same in the language's terms, but at agent scope
-                // its release writes back the XCD's L2 in every workgroup's
-                // epilogue (2-6 % slower on launches of several rounds).
-                const uint32_t prev = __hip_atomic_fetch_max(bo.ws, bc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                asm volatile("; fold returned %0" : : "v"(prev) : "memory");
-                const uint32_t done = __hip_atomic_fetch_add(bo.ws + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (done == gridDim.x - 1) {
-                    const uint32_t a = __hip_atomic_exchange(bo.ws, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_store(bo.ws + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    uint32_t fl;
-                    *bo.bias = bias_of_fmt(bo.fmt, a, bo.margin, &fl);
-                    if (amax_out) *amax_out = a;
-                    if (bo.flags) *bo.flags = fl;
-                }
-            }
+            if (AMAX) fold_amax(canon_amax(b), amax_out, bo);
             if (QF >= 0) {  // bf16 magnitude pattern
                 qo.parts[blockIdx.x] = b >> 16;
                 if (blockIdx.x == 0) *qo.used = bq_used(qo.pred);
@@ -633,109 +435,18 @@ template <int FA, int FB, int OUT_DT, bool AMAX, int QF = -1, int TN2 = 0>
 __global__ __launch_bounds__(kMainThreads) void gemm_nt_256(
     const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, const int32_t* __restrict__ ba_p,
     const int32_t* __restrict__ bb_p, void* __restrict__ C, int M, int N, int K, int tiles_m,
-    int tiles_n, int vec_out, uint32_t* __restrict__ amax_out, QuantOut qo, BiasOut bo, int ba_rows,
+    int tiles_n, uint32_t* __restrict__ amax_out, QuantOut qo, BiasOut bo, int ba_rows,
     int g1, int tiles_n2) {
     __shared__ __attribute__((aligned(1024))) uint8_t smem[kSmemBytes];
     const int b = blockIdx.x;
     if (TN2 == 0 || b < g1)
         gemm_tile<FA, FB, OUT_DT, AMAX, QF, 256>(smem, b, TN2 == 0 ? (int)gridDim.x : g1, A, B, ba_p, bb_p, C, M, N,
-                                                 K, tiles_m, tiles_n, 0, vec_out, amax_out, qo, bo, ba_rows);
+                                                 K, tiles_m, tiles_n, 0, amax_out, qo, bo, ba_rows);
     else
         gemm_tile<FA, FB, OUT_DT, AMAX, -1, (TN2 > 0 ? TN2 : 256)>(smem, b - g1, (int)gridDim.x - g1, A, B, ba_p,
                                                                    bb_p, C, M, N, K, tiles_m, tiles_n2, tiles_n * kBN,
-                                                                   vec_out, amax_out, qo, bo, ba_rows);
+                                                                   amax_out, qo, bo, ba_rows);
 }
-
-// ------------------------------------------------------------ fallback kernel
-constexpr int kSBM = 64, kSBN = 64;
-
-template <int FA, int FB, int OUT_DT, bool AMAX>
-__global__ __launch_bounds__(kThreads) void gemm_nt_small(
-    const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, const int32_t* __restrict__ ba_p,
-    const int32_t* __restrict__ bb_p, void* __restrict__ C, int64_t M, int64_t N, int64_t K,
-    int64_t tiles_n, int vec_out, uint32_t* __restrict__ amax_out, int ba_rows) {
-    __shared__ __attribute__((aligned(16))) uint8_t sa[kSBM * kBK];
-    __shared__ __attribute__((aligned(16))) uint8_t sb[kSBN * kBK];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t m0 = (blockIdx.x / tiles_n) * kSBM, n0 = (blockIdx.x % tiles_n) * kSBN;
-    // loader: thread -> row (tid / 4), logical chunks 2 (tid % 4), +1
-    const int lr = threadIdx.x >> 2, lq = threadIdx.x & 3;
-    const int wm = w >> 1, wn = w & 1;
-    const int frow = lane & 15, fg = lane >> 4;
-    const int fo0 = frow * kBK + (((2 * fg) ^ chunk_swz(frow)) << 4);
-    const int fo1 = frow * kBK + (((2 * fg + 1) ^ chunk_swz(frow)) << 4);
-
-    v4f acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-
-    // K a multiple of 16 with 16-byte aligned operands: every row starts on a
-    // 16-byte boundary and each 16-byte chunk lies wholly inside or wholly
-    // past the row, so chunks are loaded whole (zero past the row end).
-    const bool v16 = (K & 15) == 0 && (((uintptr_t)A | (uintptr_t)B) & 15) == 0;
-    for (int64_t k0 = 0; k0 < K; k0 += kBK) {
-#pragma unroll
-        for (int op = 0; op < 2; ++op) {
-            const uint8_t* src = op == 0 ? A : B;
-            const int64_t r = (op == 0 ? m0 : n0) + lr;
-            const int64_t rmax = op == 0 ? M : N;
-            uint8_t* dst = op == 0 ? sa : sb;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int c = 2 * lq + h;  // logical 16-byte chunk
-                uint4 v = make_uint4(0, 0, 0, 0);
-                if (v16) {
-                    const int64_t k = k0 + c * 16;
-                    if (r < rmax && k < K) v = *(const uint4*)(src + r * K + k);
-                } else {
-                    uint32_t wv[4] = {0, 0, 0, 0};
-                    for (int t = 0; t < 16; ++t) {
-                        const int64_t k = k0 + c * 16 + t;
-                        uint32_t byte = 0;
-                        if (r < rmax && k < K) byte = src[r * K + k];
-                        wv[t >> 2] |= byte << (8 * (t & 3));
-                    }
-                    v = make_uint4(wv[0], wv[1], wv[2], wv[3]);
-                }
-                *(uint4*)(dst + lr * kBK + ((c ^ chunk_swz(lr)) << 4)) = v;
-            }
-        }
-        __syncthreads();
-        v8i bf[2], af[2];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const uint8_t* p = sb + (wn * 32 + j * 16) * kBK;
-            const uint4 p0 = *(const uint4*)(p + fo0), p1 = *(const uint4*)(p + fo1);
-            bf[j] = v8i{(int)p0.x, (int)p0.y, (int)p0.z, (int)p0.w, (int)p1.x, (int)p1.y, (int)p1.z, (int)p1.w};
-            const uint8_t* q = sa + (wm * 32 + j * 16) * kBK;
-            const uint4 q0 = *(const uint4*)(q + fo0), q1 = *(const uint4*)(q + fo1);
-            af[j] = v8i{(int)q0.x, (int)q0.y, (int)q0.z, (int)q0.w, (int)q1.x, (int)q1.y, (int)q1.z, (int)q1.w};
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = mfma16<FB, FA>(bf[j], af[i], acc[i][j]);
-        __syncthreads();
-    }
-
-    uint32_t mx = 0;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int64_t m = m0 + wm * 32 + i * 16 + frow;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int64_t n = n0 + wn * 32 + j * 16 + fg * 4;
-            if (n < N) mx = max(mx, store4<OUT_DT>(C, N, m, n, M, N, acc[i][j], row_shift(ba_p, ba_rows, *bb_p, m, M), vec_out != 0));
-        }
-    }
-    if (AMAX) {
-        mx = wave_max_u32(mx);
-        if (lane == 0) atomicMax(amax_out, canon_amax(mx));
-    }
-}
-
 
 // ------------------------------------------------------------ decode kernel
 // M <= 32 (token-by-token inference): the product is bound by streaming B
@@ -767,7 +478,7 @@ __device__ __forceinline__ v8i ld_frag_stream(const uint8_t* p) {
 template <int FA, int FB, int OUT_DT, bool AMAX, int MB, int NB, int kDecWaves>
 __global__ __launch_bounds__(kDecWaves * 64) void gemm_nt_decode(
     const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, const int32_t* __restrict__ ba_p,
-    const int32_t* __restrict__ bb_p, void* __restrict__ C, int M, int N, int K, int vec_out,
+    const int32_t* __restrict__ bb_p, void* __restrict__ C, int M, int N, int K,
     uint32_t* __restrict__ amax_out, int ba_rows) {
     __shared__ __attribute__((aligned(16))) float red[kDecWaves][MB][NB][64][4];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -833,7 +544,7 @@ __global__ __launch_bounds__(kDecWaves * 64) void gemm_nt_decode(
         for (int ww = 1; ww < kDecWaves; ++ww) sum += *(const v4f*)red[ww][mb][j][l];
         const int64_t m = mb * 16 + (l & 15);
         const int64_t n = n0 + j * 16 + (l >> 4) * 4;
-        if (n < N) mx = max(mx, store4<OUT_DT>(C, N, m, n, M, N, sum, row_shift(ba_p, ba_rows, *bb_p, m, M), vec_out != 0));
+        if (n < N) mx = max(mx, store4<OUT_DT>(C, N, m, n, M, N, sum, row_shift(ba_p, ba_rows, *bb_p, m, M)));
     }
     if (AMAX) {
         mx = wave_max_u32(mx);
@@ -858,7 +569,7 @@ constexpr int kDlKC = 512, kDlBuf = 3;
 template <int FA, int FB, int OUT_DT, bool AMAX, int BR>
 __global__ __launch_bounds__(256) void gemm_nt_decode_lds(
     const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, const int32_t* __restrict__ ba_p,
-    const int32_t* __restrict__ bb_p, void* __restrict__ C, int M, int N, int K, int vec_out,
+    const int32_t* __restrict__ bb_p, void* __restrict__ C, int M, int N, int K,
     uint32_t* __restrict__ amax_out, int ba_rows) {
     constexpr int kRows = BR + 16, kStage = kRows * kDlKC, kCpr = kDlKC / 16;
     constexpr int kNi = kRows / 2;  // copies per stage, two rows each
@@ -923,7 +634,7 @@ __global__ __launch_bounds__(256) void gemm_nt_decode_lds(
 #pragma unroll
         for (int hh = 1; hh < kWpb; ++hh) sum += *(const v4f*)red[w + hh * kNbb][lane];
         const int64_t m = lane & 15, n = n0 + w * 16 + (lane >> 4) * 4;
-        if (n < N) mx = store4<OUT_DT>(C, N, m, n, M, N, sum, row_shift(ba_p, ba_rows, *bb_p, m, M), vec_out != 0);
+        if (n < N) mx = store4<OUT_DT>(C, N, m, n, M, N, sum, row_shift(ba_p, ba_rows, *bb_p, m, M));
     }
     if (AMAX) {
         mx = wave_max_u32(mx);
@@ -933,13 +644,13 @@ __global__ __launch_bounds__(256) void gemm_nt_decode_lds(
 
 template <int FA, int FB, int OUT_DT, bool AMAX, int MB>
 void launch_decode(const uint8_t* A, const int32_t* ba, const uint8_t* B, const int32_t* bb, void* C,
-                   int M, int N, int K, int vec_out, uint32_t* amax, int ba_rows, hipStream_t s) {
+                   int M, int N, int K, uint32_t* amax, int ba_rows, hipStream_t s) {
     // 32 output columns per workgroup of 4 waves, each wave a quarter of the
     // K range (the best of 1-8 column blocks x 4-16 waves on the Llama-2-70B
     // decode shapes)
     const int nblk = (N + 31) / 32;
     hipLaunchKernelGGL((gemm_nt_decode<FA, FB, OUT_DT, AMAX, MB, 2, 4>), dim3(nblk), dim3(4 * 64), 0, s, A, B, ba,
-                       bb, C, M, N, K, vec_out, amax, ba_rows);
+                       bb, C, M, N, K, amax, ba_rows);
 }
 
 __global__ void fill_u32_kernel(uint32_t* p, uint32_t v) {
@@ -990,43 +701,38 @@ void narrow_split(int tiles_m, int tiles_n, int64_t N, int& ndp, int& tw, int& t
     }
 }
 
-// bo.ws != nullptr only where the 256-row kernel runs (fast_path, M > 32).
+// bo.ws != nullptr only where the 256-row or the ragged kernels run.
 template <int FA, int FB, int OUT_DT, bool AMAX>
 void launch_t(const uint8_t* A, const int32_t* ba, const uint8_t* B, const int32_t* bb, void* C,
               int64_t M, int64_t N, int64_t K, uint32_t* amax, const BiasOut& bo, int ba_rows, hipStream_t s) {
-    const int esz = OUT_DT == FP8_DT_BF16 ? 2 : 4;
-    const int vec_out = ((uintptr_t)C % (4 * esz) == 0) && (N % 4 == 0);
     const bool fast = fast_path(A, B, M, N, K);
     if (fast && M <= 16 && K % kDlKC == 0) {
         // 64 weight rows per workgroup unless that leaves fewer than 256
         // workgroups streaming long rows (measured on the Llama-2-70B shapes)
         if (N >= 64 * 256 || K <= 8192)
             hipLaunchKernelGGL((gemm_nt_decode_lds<FA, FB, OUT_DT, AMAX, 64>), dim3((unsigned)((N + 63) / 64)), dim3(256),
-                               0, s, A, B, ba, bb, C, (int)M, (int)N, (int)K, vec_out, amax, ba_rows);
+                               0, s, A, B, ba, bb, C, (int)M, (int)N, (int)K, amax, ba_rows);
         else
             hipLaunchKernelGGL((gemm_nt_decode_lds<FA, FB, OUT_DT, AMAX, 32>), dim3((unsigned)((N + 31) / 32)), dim3(256),
-                               0, s, A, B, ba, bb, C, (int)M, (int)N, (int)K, vec_out, amax, ba_rows);
+                               0, s, A, B, ba, bb, C, (int)M, (int)N, (int)K, amax, ba_rows);
     } else if (fast && M <= 32) {
-        if (M <= 16) launch_decode<FA, FB, OUT_DT, AMAX, 1>(A, ba, B, bb, C, (int)M, (int)N, (int)K, vec_out, amax, ba_rows, s);
-        else launch_decode<FA, FB, OUT_DT, AMAX, 2>(A, ba, B, bb, C, (int)M, (int)N, (int)K, vec_out, amax, ba_rows, s);
+        if (M <= 16) launch_decode<FA, FB, OUT_DT, AMAX, 1>(A, ba, B, bb, C, (int)M, (int)N, (int)K, amax, ba_rows, s);
+        else launch_decode<FA, FB, OUT_DT, AMAX, 2>(A, ba, B, bb, C, (int)M, (int)N, (int)K, amax, ba_rows, s);
     } else if (fast) {
         const int tiles_m = (int)((M + kBM - 1) / kBM), tiles_n = (int)((N + kBN - 1) / kBN);
-        const int vec16 = ((uintptr_t)C % 16 == 0) && ((N * esz) % 16 == 0);
         int ndp, tw, tn2;
         narrow_split(tiles_m, tiles_n, N, ndp, tw, tn2);
         const int g1 = tiles_m * ndp, grid = g1 + tiles_m * tn2;
 #define FP8LIN_GEMM256(TW)                                                                                         \
     hipLaunchKernelGGL((gemm_nt_256<FA, FB, OUT_DT, AMAX, -1, TW>), dim3(grid), dim3(kMainThreads), 0, s, A, B, ba, \
-                       bb, C, (int)M, (int)N, (int)K, tiles_m, ndp, vec16, amax, QuantOut{}, bo, ba_rows, g1, tn2)
+                       bb, C, (int)M, (int)N, (int)K, tiles_m, ndp, amax, QuantOut{}, bo, ba_rows, g1, tn2)
         if (tw == 64) FP8LIN_GEMM256(64);
         else if (tw == 128) FP8LIN_GEMM256(128);
         else if (tw == 192) FP8LIN_GEMM256(192);
         else FP8LIN_GEMM256(0);
 #undef FP8LIN_GEMM256
     } else {
-        const int64_t tiles_m = (M + kSBM - 1) / kSBM, tiles_n = (N + kSBN - 1) / kSBN;
-        hipLaunchKernelGGL((gemm_nt_small<FA, FB, OUT_DT, AMAX>), dim3((unsigned)(tiles_m * tiles_n)),
-                           dim3(kThreads), 0, s, A, B, ba, bb, C, M, N, K, tiles_n, vec_out, amax, ba_rows);
+        launch_gemm_ragged(FA, FB, MmArgs{A, B, ba, bb, C, M, N, K, OUT_DT, AMAX, amax, bo, ba_rows}, s);
     }
 }
 
@@ -1051,19 +757,16 @@ void dispatch_fmts(const uint8_t* A, int fa, const int32_t* ba, const uint8_t* B
         dispatch_out<FP8_E4M3, FP8_E4M3>(A, ba, B, bb, C, out_dt, M, N, K, with_amax, amax, bo, ba_rows, s);
     else if (fa == FP8_E5M2 && fb == FP8_E4M3)
         dispatch_out<FP8_E5M2, FP8_E4M3>(A, ba, B, bb, C, out_dt, M, N, K, with_amax, amax, bo, ba_rows, s);
-    else if (fa == FP8_E4M3 && fb == FP8_E5M2)
+    else  // the ABI's products: E4 x E4, E5 x E4, E4 x E5
         dispatch_out<FP8_E4M3, FP8_E5M2>(A, ba, B, bb, C, out_dt, M, N, K, with_amax, amax, bo, ba_rows, s);
-    else
-        dispatch_out<FP8_E5M2, FP8_E5M2>(A, ba, B, bb, C, out_dt, M, N, K, with_amax, amax, bo, ba_rows, s);
 }
 
 template <int FA, int FB, int QF>
 void launch_fused_t(const uint8_t* A, const int32_t* ba, const uint8_t* B, const int32_t* bb, void* C,
                     int64_t M, int64_t N, int64_t K, const QuantOut& qo, hipStream_t s) {
     const int tiles_m = (int)((M + kBM - 1) / kBM), tiles_n = (int)((N + kBN - 1) / kBN);
-    const int vec16 = ((uintptr_t)C % 16 == 0) && ((N * 2) % 16 == 0);
     hipLaunchKernelGGL((gemm_nt_256<FA, FB, FP8_DT_BF16, false, QF>), dim3(tiles_m * tiles_n), dim3(kMainThreads), 0,
-                       s, A, B, ba, bb, C, (int)M, (int)N, (int)K, tiles_m, tiles_n, vec16, nullptr, qo, BiasOut{}, 0,
+                       s, A, B, ba, bb, C, (int)M, (int)N, (int)K, tiles_m, tiles_n, nullptr, qo, BiasOut{}, 0,
                        tiles_m * tiles_n, 0);
 }
 
@@ -1107,8 +810,6 @@ int32_t launch_gemm_nt_quantise(const uint8_t* A, int fa, const int32_t* ba, con
     qo.ldy8 = ldy8;
     qo.y8t = y8t;
     qo.ldy8t = ldy8t;
-    qo.vec8 = ((uintptr_t)y8 % 16 == 0) && (ldy8 % 16 == 0);
-    qo.vec8t = y8t && ((uintptr_t)y8t % 16 == 0) && (ldy8t % 16 == 0);
     if (fa == FP8_E4M3)
         fused_fmt<FP8_E4M3, FP8_E4M3>(qfmt, A, ba, B, bb, C, M, N, K, qo, s);
     else
@@ -1137,12 +838,12 @@ int32_t launch_gemm_nt_bias(const uint8_t* A, int fa, const int32_t* ba, const u
                             const int32_t* bb, void* C, int out_dt, int64_t M, int64_t N, int64_t K, int bfmt,
                             int32_t margin, int32_t* bias, uint32_t* amax_bits, uint32_t* flags, uint32_t* ws,
                             hipStream_t s, int ba_rows) {
-    if (fast_path(A, B, M, N, K) && M > 32) {
+    if (!(fast_path(A, B, M, N, K) && M <= 32)) {
         dispatch_fmts(A, fa, ba, B, fb, bb, C, out_dt, M, N, K, true, amax_bits, BiasOut{bias, flags, ws, bfmt, margin},
                       ba_rows, s);
         return hip_status();
     }
-    // decode and fallback kernels: amax with atomics into a zeroed word (ws[0]
+    // decode kernels: amax with atomics into a zeroed word (ws[0]
     // if no amax output is wanted, zeroed again afterwards), then the bias
     uint32_t* acc = amax_bits ? amax_bits : ws;
     hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, acc, 0u);

@@ -80,6 +80,34 @@ int32_t launch_gemm_nt_quantise(const uint8_t* A, int fa, const int32_t* ba, con
                                 uint32_t* flags, uint8_t* y8, int64_t ldy8, uint8_t* y8t, int64_t ldy8t,
                                 uint32_t* ws, hipStream_t s);
 
+// Eq. 3 bias of a matmul's output taken in the same launch (ws != nullptr):
+// every workgroup folds its largest |Y| pattern into ws[0] and then counts
+// itself in ws[1]; the last one to count takes the total, writes amax, bias
+// and flags, and leaves both words zero for the next call.
+struct BiasOut {
+    int32_t* bias;
+    uint32_t* flags;  // may be null
+    uint32_t* ws;     // [0] running maximum, [1] finished workgroups; zero between calls
+    int fmt;
+    int32_t margin;
+};
+
+// Operands and outputs of one matmul (see launch_gemm_nt).
+struct MmArgs {
+    const uint8_t *A, *B;
+    const int32_t *ba, *bb;
+    void* C;
+    int64_t M, N, K;
+    int out_dt;
+    int with_amax;   // epilogue amax, into *amax or folded into bo.ws
+    uint32_t* amax;  // may be null with bo.ws
+    BiasOut bo;      // bo.ws may be null
+    int ba_rows;
+};
+
+// The kernels for K not a multiple of 128 (or K >= 2^22): fp8lin_gemm_ragged.hip.
+void launch_gemm_ragged(int fa, int fb, const MmArgs& a, hipStream_t s);
+
 // C[m, n] = 2^-(*ba + *bb) * sum_k A[m, k] * B[n, k]; A [M, K] (format fa),
 // B [N, K] (format fb), both dense; C [M, N] dense of type out_dt.  With
 // ba_rows, ba holds one bias per row of A: 2^-(ba[m] + *bb).
