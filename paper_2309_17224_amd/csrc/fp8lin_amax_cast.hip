@@ -35,53 +35,49 @@ namespace {
 // than a grid-stride sweep (about 7 vs 5.5 TB/s on a 2 GiB buffer).
 template <int DT>
 __global__ __launch_bounds__(kAmaxThreads) void amax_partial_kernel(const void* __restrict__ x,
-                                                                   int64_t n, int vec,
+                                                                   int64_t n,
                                                                    uint32_t* __restrict__ partial) {
     __shared__ uint32_t red[kAmaxThreads / 64];
     constexpr int kL = 8;
     uint32_t m = 0;
-    int64_t tail0 = 0;
-    if (vec) {
-        constexpr int per = DT == FP8_DT_BF16 ? 8 : 4;
-        const uint4* __restrict__ p = (const uint4*)x;
-        const int64_t nv = n / per;
-        tail0 = nv * per;
-        const int64_t chunk = ((nv + gridDim.x - 1) / gridDim.x + 255) & ~(int64_t)255;
-        const int64_t b0 = min(nv, (int64_t)blockIdx.x * chunk), b1 = min(nv, b0 + chunk);
-        int64_t i = b0 + threadIdx.x;
-        us2 mm = {0, 0};
-        auto fold = [&](const uint4& v) {
-            if (DT == FP8_DT_BF16) mm = fold_bf16(mm, v);
-            else m = fold_f32(m, v);
-        };
-        for (; i + (kL - 1) * kAmaxThreads < b1; i += kL * kAmaxThreads) {
-            uint4 v[kL];
+    constexpr int per = DT == FP8_DT_BF16 ? 8 : 4;
+    const u32x4_any* __restrict__ p = (const u32x4_any*)x;  // x at any alignment
+    const int64_t nv = n / per;
+    const int64_t tail0 = nv * per;
+    const int64_t chunk = ((nv + gridDim.x - 1) / gridDim.x + 255) & ~(int64_t)255;
+    const int64_t b0 = min(nv, (int64_t)blockIdx.x * chunk), b1 = min(nv, b0 + chunk);
+    int64_t i = b0 + threadIdx.x;
+    us2 mm = {0, 0};
+    auto fold = [&](const uint4& v) {
+        if (DT == FP8_DT_BF16) mm = fold_bf16(mm, v);
+        else m = fold_f32(m, v);
+    };
+    for (; i + (kL - 1) * kAmaxThreads < b1; i += kL * kAmaxThreads) {
+        uint4 v[kL];
 #pragma unroll
-            for (int l = 0; l < kL; ++l) v[l] = ld_stream(p + i + l * kAmaxThreads);
-            // all kL loads issue before the first use (the scheduler would
-            // otherwise start folding the first one and wait for it alone)
-            __builtin_amdgcn_sched_barrier(0);
+        for (int l = 0; l < kL; ++l) v[l] = ld_stream(p + i + l * kAmaxThreads);
+        // all kL loads issue before the first use (the scheduler would
+        // otherwise start folding the first one and wait for it alone)
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int l = 0; l < kL; ++l) fold(v[l]);
-        }
-        // fewer than kL vectors of this lane left: unconditional loads of
-        // in-range vectors (a guarded load compiles to a branch and a wait per
-        // load), those past the range replaced by zero, neutral for the maximum
-        if (b1 > b0) {
-            uint4 v[kL];
-#pragma unroll
-            for (int l = 0; l < kL; ++l) v[l] = ld_stream(p + min(i + l * kAmaxThreads, b1 - 1));
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int l = 0; l < kL; ++l)
-                if (i + l * kAmaxThreads >= b1) v[l] = make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-            for (int l = 0; l < kL; ++l) fold(v[l]);
-        }
-        if (DT == FP8_DT_BF16) m = max((uint32_t)mm.x, (uint32_t)mm.y);
+        for (int l = 0; l < kL; ++l) fold(v[l]);
     }
-    // elements past the last whole vector (or every element when x is not
-    // 16-byte aligned), strided over the whole grid
+    // fewer than kL vectors of this lane left: unconditional loads of
+    // in-range vectors (a guarded load compiles to a branch and a wait per
+    // load), those past the range replaced by zero, neutral for the maximum
+    if (b1 > b0) {
+        uint4 v[kL];
+#pragma unroll
+        for (int l = 0; l < kL; ++l) v[l] = ld_stream(p + min(i + l * kAmaxThreads, b1 - 1));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int l = 0; l < kL; ++l)
+            if (i + l * kAmaxThreads >= b1) v[l] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+        for (int l = 0; l < kL; ++l) fold(v[l]);
+    }
+    if (DT == FP8_DT_BF16) m = max((uint32_t)mm.x, (uint32_t)mm.y);
+    // elements past the last whole vector, strided over the whole grid
     const int64_t tid = (int64_t)blockIdx.x * kAmaxThreads + threadIdx.x;
     const int64_t nth = (int64_t)gridDim.x * kAmaxThreads;
     for (int64_t j = tail0 + tid; j < n; j += nth) m = max(m, elem_mag<DT>(x, j));
@@ -136,8 +132,7 @@ template <int DT, int FMT, bool MAX, bool ROWB = false>
 __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_t rows, int64_t cols,
                                               int64_t ldx, int b, uint8_t* __restrict__ q, int64_t ldq,
                                               uint8_t* __restrict__ qT, int64_t ldqT, int64_t tr,
-                                              int64_t tc, int vec_in, int vec_q, int vec_qT,
-                                              uint8_t* __restrict__ tile,
+                                              int64_t tc, uint8_t* __restrict__ tile,
                                               const int32_t* __restrict__ rowb = nullptr) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int chunk = lane & 15, g = lane >> 4;
@@ -146,16 +141,44 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
     const int64_t r0 = R0 + lr, c0 = C0 + lc;
     int bi[kRpt];  // bias of each of this lane's rows
 #pragma unroll
-    for (int i = 0; i < kRpt; ++i) bi[i] = ROWB ? (r0 + i < rows ? clamp_bias(rowb[r0 + i]) : 0) : b;
+    for (int i = 0; i < kRpt; ++i) bi[i] = ROWB ? clamp_bias(rowb[min(r0 + i, rows - 1)]) : b;
 
     uint32_t lo[kRpt], hi[kRpt];  // codes of columns c0..c0+3 and c0+4..c0+7, per row
     uint32_t mag = 0;
-    const bool full = vec_in && (r0 + kRpt <= rows) && (c0 + 8 <= cols);
-    if (full) {
+    // Rows past the last one read the last row again (not stored; a copy of
+    // real elements cannot change the maximum), so only the columns of a
+    // lane's block decide how it loads: eight whole columns, the last ones of
+    // the row (one vector ending at the row's end, moved down, zeros beyond),
+    // or, in rows of fewer than eight columns, element by element.  One lane
+    // on a partial block used to go element by element, 64 guarded loads in a
+    // row, and kept the whole launch waiting; transposed codes with an odd row
+    // stride left as single bytes.  fp8_quantise of 301 x 4096: 13.0 -> 7.2 us;
+    // 1531 x 4096 with transposed codes: 25.0 -> 12.9 us; whole tiles as before
+    // (4096 x 11008 with both copies 36 us, 5.0 TB/s).
+    const int64_t last = rows - 1;
+    const int64_t left = cols - c0;  // columns of the row from c0 on
+    const bool whole = R0 + kCastRows <= rows && C0 + kCastCols <= cols;  // of the tile: uniform
+    int64_t at = (whole ? r0 : min(r0, last)) * ldx + c0;
+    auto next_row = [&](int i) { at += whole || r0 + i < last ? ldx : 0; };
+    if (cols >= 8) {
+        const int drop = whole || left >= 8 ? 0 : left > 0 ? (int)(8 - left) : 8;  // elements moved out
+        at -= drop;
         if (DT == FP8_DT_BF16) {
             uint4 v[kRpt];
+            if (whole) {
 #pragma unroll
-            for (int i = 0; i < kRpt; ++i) v[i] = ld_stream((const uint16_t*)x + (r0 + i) * ldx + c0);
+                for (int i = 0; i < kRpt; ++i) v[i] = ld_stream((const uint16_t*)x + at + i * ldx);
+            } else {
+#pragma unroll
+                for (int i = 0; i < kRpt; ++i) {
+                    v[i] = ld_stream((const uint16_t*)x + (left > 0 ? at : 0));
+                    next_row(i);
+                }
+            }
+            if (drop) {
+#pragma unroll
+                for (int i = 0; i < kRpt; ++i) v[i] = shr128(v[i], 16 * drop);
+            }
             if (MAX) {
                 us2 mm = {0, 0};
 #pragma unroll
@@ -176,8 +199,15 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
         } else {
 #pragma unroll
             for (int i = 0; i < kRpt; ++i) {
-                const uint4* p = (const uint4*)((const uint32_t*)x + (r0 + i) * ldx + c0);
-                const uint4 a = ld_stream(p), bb = ld_stream(p + 1);
+                const uint32_t* p = (const uint32_t*)x + (left > 0 ? at : 0);
+                uint4 a = ld_stream(p), bb = ld_stream(p + 4);
+                next_row(i);
+                if (drop) {
+                    if (drop & 8) a = bb = make_uint4(0u, 0u, 0u, 0u);
+                    if (drop & 4) a = bb, bb = make_uint4(0u, 0u, 0u, 0u);
+                    if (drop & 2) a = make_uint4(a.z, a.w, bb.x, bb.y), bb = make_uint4(bb.z, bb.w, 0u, 0u);
+                    if (drop & 1) a = make_uint4(a.y, a.z, a.w, bb.x), bb = make_uint4(bb.y, bb.z, bb.w, 0u);
+                }
                 if (MAX) mag = fold_f32(fold_f32(mag, a), bb);
                 lo[i] = cast4_f32<FMT>(a, bi[i]);
                 hi[i] = cast4_f32<FMT>(bb, bi[i]);
@@ -195,29 +225,35 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
         for (int i = 0; i < kRpt; ++i) {
             uint32_t wlo = 0, whi = 0;
             for (int j = 0; j < 8; ++j) {
-                const int64_t r = r0 + i, c = c0 + j;
                 uint32_t code = 0u;
-                if (r < rows && c < cols) {
-                    code = cast1<DT, FMT>(x, r * ldx + c, bi[i]);
-                    if (MAX) mag = max(mag, elem_mag<DT>(x, r * ldx + c));
+                if (j < left) {
+                    code = cast1<DT, FMT>(x, at + j, bi[i]);
+                    if (MAX) mag = max(mag, elem_mag<DT>(x, at + j));
                 }
                 if (j < 4) wlo |= code << (8 * j); else whi |= code << (8 * (j - 4));
             }
+            next_row(i);
             lo[i] = wlo;
             hi[i] = whi;
         }
     }
 
     if (q) {
-        if (full && vec_q) {
+        uint8_t* o = q + r0 * ldq + c0;
+        if (whole) {
 #pragma unroll
-            for (int i = 0; i < kRpt; ++i) *(uint2*)(q + (r0 + i) * ldq + c0) = make_uint2(lo[i], hi[i]);
+            for (int i = 0; i < kRpt; ++i) st8_any(o + i * ldq, lo[i], hi[i]);
         } else {
-            for (int i = 0; i < kRpt; ++i)
-                for (int j = 0; j < 8; ++j) {
-                    const int64_t r = r0 + i, c = c0 + j;
-                    if (r < rows && c < cols) q[r * ldq + c] = (uint8_t)byte_of(j < 4 ? lo[i] : hi[i], j & 3);
+#pragma unroll
+            for (int i = 0; i < kRpt; ++i, o += ldq) {
+                if (r0 + i >= rows) break;
+                if (left >= 8) {
+                    st8_any(o, lo[i], hi[i]);
+                } else {
+                    for (int j = 0; j < 8; ++j)
+                        if (j < left) o[j] = (uint8_t)byte_of(j < 4 ? lo[i] : hi[i], j & 3);
                 }
+            }
         }
     }
 
@@ -248,8 +284,8 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
             if (c >= cols || rr >= rows) continue;
             const uint4 v = *(const uint4*)(tile + cl * kCastRows + (((qq ^ (cl >> 3)) & 7) << 4));
             uint8_t* dst = qT + c * ldqT + rr;
-            if (vec_qT && rr + 16 <= rows) {
-                *(uint4*)dst = v;
+            if (rr + 16 <= rows) {
+                st16_any(dst, v);
             } else {
                 const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
                 for (int t = 0; t < 16 && rr + t < rows; ++t) dst[t] = (uint8_t)byte_of(wv[t >> 2], t & 3);
@@ -265,11 +301,11 @@ template <int DT, int FMT>
 __global__ __launch_bounds__(kCastThreads) void cast_kernel(
     const void* __restrict__ x, int64_t rows, int64_t cols, int64_t ldx,
     const int32_t* __restrict__ bias_p, uint8_t* __restrict__ q, int64_t ldq,
-    uint8_t* __restrict__ qT, int64_t ldqT, int64_t tiles_c, int vec_in, int vec_q, int vec_qT) {
+    uint8_t* __restrict__ qT, int64_t ldqT, int64_t tiles_c) {
     __shared__ __attribute__((aligned(16))) uint8_t tile[kCastCols * kCastRows];
     const int b = clamp_bias(*bias_p);
     cast_tile<DT, FMT, false>(x, rows, cols, ldx, b, q, ldq, qT, ldqT, blockIdx.x / tiles_c,
-                              blockIdx.x % tiles_c, vec_in, vec_q, vec_qT, tile);
+                              blockIdx.x % tiles_c, tile);
 }
 
 // ------------------------------------------------- quantise: amax + bias + cast
@@ -286,8 +322,7 @@ template <int DT, int FMT, bool CAST>
 __global__ __launch_bounds__(kCastThreads) void quant_pass1_kernel(
     const void* __restrict__ x, int64_t rows, int64_t cols, int64_t ldx,
     const int32_t* __restrict__ bias_pred, int32_t* __restrict__ used, uint32_t* __restrict__ parts,
-    uint8_t* __restrict__ q, int64_t ldq, uint8_t* __restrict__ qT, int64_t ldqT, int64_t tiles_c,
-    int vec_in, int vec_q, int vec_qT) {
+    uint8_t* __restrict__ q, int64_t ldq, uint8_t* __restrict__ qT, int64_t ldqT, int64_t tiles_c) {
     __shared__ __attribute__((aligned(16))) uint8_t tile[kCastCols * kCastRows];
     __shared__ uint32_t red[kCastThreads / 64];
     int b = 0;
@@ -297,7 +332,7 @@ __global__ __launch_bounds__(kCastThreads) void quant_pass1_kernel(
     }
     const uint32_t m = cast_tile<DT, FMT, true>(x, rows, cols, ldx, b, CAST ? q : nullptr, ldq,
                                                 CAST ? qT : nullptr, ldqT, blockIdx.x / tiles_c,
-                                                blockIdx.x % tiles_c, vec_in, vec_q, vec_qT, tile);
+                                                blockIdx.x % tiles_c, tile);
     const uint32_t bm = block_max(m, red);
     if (threadIdx.x == 0) parts[blockIdx.x] = bm;
 }
@@ -309,8 +344,7 @@ __device__ __forceinline__ void quant_pass2_body(
     int64_t rows, int64_t cols, int64_t ldx, const uint32_t* __restrict__ parts, int nparts,
     const int32_t* __restrict__ used, int have_used, int32_t margin, int32_t* __restrict__ bias,
     uint32_t* __restrict__ amax_bits, uint32_t* __restrict__ flags, uint8_t* __restrict__ q, int64_t ldq,
-    uint8_t* __restrict__ qT, int64_t ldqT, int64_t tiles_c, int64_t ncast, int vec_in, int vec_q,
-    int vec_qT) {
+    uint8_t* __restrict__ qT, int64_t ldqT, int64_t tiles_c, int64_t ncast) {
     uint32_t m = strided_max<kCastThreads>(parts, nparts);
     m = block_max(m, red);
     if (threadIdx.x == 0) amax_s = m;
@@ -326,8 +360,7 @@ __device__ __forceinline__ void quant_pass2_body(
     const int b = clamp_bias(bx);
     if (have_used && *used == b) return;  // pass 1 already wrote these codes
     for (int64_t t = bid; t < ncast; t += nb)
-        cast_tile<DT, FMT, false>(x, rows, cols, ldx, b, q, ldq, qT, ldqT, t / tiles_c, t % tiles_c,
-                                  vec_in, vec_q, vec_qT, tile);
+        cast_tile<DT, FMT, false>(x, rows, cols, ldx, b, q, ldq, qT, ldqT, t / tiles_c, t % tiles_c, tile);
 }
 
 template <int DT, int FMT>
@@ -336,13 +369,12 @@ __global__ __launch_bounds__(kCastThreads) void quant_pass2_kernel(
     const uint32_t* __restrict__ parts, int nparts, const int32_t* __restrict__ used, int have_used,
     int32_t margin, int32_t* __restrict__ bias, uint32_t* __restrict__ amax_bits,
     uint32_t* __restrict__ flags, uint8_t* __restrict__ q, int64_t ldq, uint8_t* __restrict__ qT,
-    int64_t ldqT, int64_t tiles_c, int64_t ncast, int vec_in, int vec_q, int vec_qT) {
+    int64_t ldqT, int64_t tiles_c, int64_t ncast) {
     __shared__ __attribute__((aligned(16))) uint8_t tile[kCastCols * kCastRows];
     __shared__ uint32_t red[kCastThreads / 64];
     __shared__ uint32_t amax_s;
     quant_pass2_body<DT, FMT>(blockIdx.x, gridDim.x, tile, red, amax_s, x, rows, cols, ldx, parts, nparts, used,
-                              have_used, margin, bias, amax_bits, flags, q, ldq, qT, ldqT, tiles_c, ncast,
-                              vec_in, vec_q, vec_qT);
+                              have_used, margin, bias, amax_bits, flags, q, ldq, qT, ldqT, tiles_c, ncast);
 }
 
 // ------------------------------------------------ delayed scaling
@@ -408,7 +440,6 @@ struct QBatch {
     uint8_t* qT[kQBatch];
     int64_t ldqT[kQBatch];
     uint32_t* ws[kQBatch];
-    int vec_in[kQBatch], vec_q[kQBatch], vec_qT[kQBatch];
 };
 
 __device__ __forceinline__ int batch_slot(const int64_t* start, int n, int64_t b) {
@@ -430,7 +461,7 @@ __global__ __launch_bounds__(kCastThreads) void quant_pass1_batch_kernel(QBatch 
     }
     const uint32_t m = cast_tile<DT, FMT, true>(qb.x[i], qb.rows[i], qb.cols[i], qb.ldx[i], b, CAST ? qb.q[i] : nullptr,
                                                 qb.ldq[i], CAST ? qb.qT[i] : nullptr, qb.ldqT[i], t / qb.tiles_c[i],
-                                                t % qb.tiles_c[i], qb.vec_in[i], qb.vec_q[i], qb.vec_qT[i], tile);
+                                                t % qb.tiles_c[i], tile);
     const uint32_t bm = block_max(m, red);
     if (threadIdx.x == 0) qb.ws[i][1 + t] = bm;
 }
@@ -445,8 +476,7 @@ __global__ __launch_bounds__(kCastThreads) void quant_pass2_batch_kernel(QBatch 
     quant_pass2_body<DT, FMT>((int)(blockIdx.x - qb.p0[i]), (int)(qb.p0[i + 1] - qb.p0[i]), tile, red, amax_s,
                               qb.x[i], qb.rows[i], qb.cols[i], qb.ldx[i], qb.ws[i] + 1, (int)ntiles,
                               (const int32_t*)qb.ws[i], have_used, margin, qb.bias[i], qb.amax[i], qb.flags[i],
-                              qb.q[i], qb.ldq[i], qb.qT[i], qb.ldqT[i], qb.tiles_c[i], ntiles, qb.vec_in[i],
-                              qb.vec_q[i], qb.vec_qT[i]);
+                              qb.q[i], qb.ldq[i], qb.qT[i], qb.ldqT[i], qb.tiles_c[i], ntiles);
 }
 
 template <int DT, int FMT>
@@ -454,12 +484,8 @@ void launch_cast_t(const void* x, int64_t rows, int64_t cols, int64_t ldx, const
                    uint8_t* q, int64_t ldq, uint8_t* qT, int64_t ldqT, hipStream_t s) {
     const int64_t tiles_r = (rows + kCastRows - 1) / kCastRows;
     const int64_t tiles_c = (cols + kCastCols - 1) / kCastCols;
-    const int esz = DT == FP8_DT_BF16 ? 2 : 4;
-    const int vec_in = ((uintptr_t)x % 16 == 0) && ((ldx * esz) % 16 == 0);
-    const int vec_q = q && ((uintptr_t)q % 8 == 0) && (ldq % 8 == 0);
-    const int vec_qT = qT && ((uintptr_t)qT % 16 == 0) && (ldqT % 16 == 0);
     hipLaunchKernelGGL((cast_kernel<DT, FMT>), dim3((unsigned)(tiles_r * tiles_c)), dim3(kCastThreads), 0,
-                       s, x, rows, cols, ldx, bias, q, ldq, qT, ldqT, tiles_c, vec_in, vec_q, vec_qT);
+                       s, x, rows, cols, ldx, bias, q, ldq, qT, ldqT, tiles_c);
 }
 
 constexpr int kQuantPass2MaxBlocks = 1024;
@@ -472,31 +498,24 @@ void launch_quantise_t(const void* x, int64_t rows, int64_t cols, int64_t ldx, i
     const int64_t tiles_r = (rows + kCastRows - 1) / kCastRows;
     const int64_t tiles_c = (cols + kCastCols - 1) / kCastCols;
     const int64_t ntiles = tiles_r * tiles_c;
-    const int esz = DT == FP8_DT_BF16 ? 2 : 4;
-    const int vec_in = ((uintptr_t)x % 16 == 0) && ((ldx * esz) % 16 == 0);
-    const int vec_q = q && ((uintptr_t)q % 8 == 0) && (ldq % 8 == 0);
-    const int vec_qT = qT && ((uintptr_t)qT % 16 == 0) && (ldqT % 16 == 0);
     int32_t* used = (int32_t*)ws;
     uint32_t* parts = ws + 1;
     if (bias_pred)
         hipLaunchKernelGGL((quant_pass1_kernel<DT, FMT, true>), dim3((unsigned)ntiles), dim3(kCastThreads), 0, s,
-                           x, rows, cols, ldx, bias_pred, used, parts, q, ldq, qT, ldqT, tiles_c, vec_in,
-                           vec_q, vec_qT);
+                           x, rows, cols, ldx, bias_pred, used, parts, q, ldq, qT, ldqT, tiles_c);
     else
         hipLaunchKernelGGL((quant_pass1_kernel<DT, FMT, false>), dim3((unsigned)ntiles), dim3(kCastThreads), 0, s,
-                           x, rows, cols, ldx, bias_pred, used, parts, q, ldq, qT, ldqT, tiles_c, vec_in,
-                           vec_q, vec_qT);
+                           x, rows, cols, ldx, bias_pred, used, parts, q, ldq, qT, ldqT, tiles_c);
     const int nb2 = (int)(ntiles < kQuantPass2MaxBlocks ? ntiles : kQuantPass2MaxBlocks);
     hipLaunchKernelGGL((quant_pass2_kernel<DT, FMT>), dim3(nb2), dim3(kCastThreads), 0, s, x, rows, cols, ldx,
                        parts, (int)ntiles, used, bias_pred ? 1 : 0, margin, bias, amax_bits, flags, q, ldq,
-                       qT, ldqT, tiles_c, ntiles, vec_in, vec_q, vec_qT);
+                       qT, ldqT, tiles_c, ntiles);
 }
 
 template <int DT, int FMT>
 void launch_quantise_batch_t(int n, const QuantDesc* d, int32_t margin, hipStream_t s) {
     QBatch qb{};
     qb.n = n;
-    const int esz = DT == FP8_DT_BF16 ? 2 : 4;
     bool pred = false;
     for (int i = 0; i < n; ++i) {
         const int64_t tiles_c = (d[i].cols + kCastCols - 1) / kCastCols;
@@ -517,9 +536,6 @@ void launch_quantise_batch_t(int n, const QuantDesc* d, int32_t margin, hipStrea
         qb.qT[i] = d[i].qT;
         qb.ldqT[i] = d[i].ldqT;
         qb.ws[i] = d[i].ws;
-        qb.vec_in[i] = ((uintptr_t)d[i].x % 16 == 0) && ((d[i].ldx * esz) % 16 == 0);
-        qb.vec_q[i] = d[i].q && ((uintptr_t)d[i].q % 8 == 0) && (d[i].ldq % 8 == 0);
-        qb.vec_qT[i] = d[i].qT && ((uintptr_t)d[i].qT % 16 == 0) && (d[i].ldqT % 16 == 0);
         pred = d[i].pred != nullptr;
     }
     if (pred)
@@ -539,14 +555,9 @@ void launch_quant_check_t(const void* x, int64_t rows, int64_t cols, int64_t ldx
                           int64_t ldqT, hipStream_t s) {
     const int64_t tiles_c = (cols + kCastCols - 1) / kCastCols;
     const int64_t ncast = ((rows + kCastRows - 1) / kCastRows) * tiles_c;
-    const int esz = DT == FP8_DT_BF16 ? 2 : 4;
-    const int vec_in = ((uintptr_t)x % 16 == 0) && ((ldx * esz) % 16 == 0);
-    const int vec_q = q && ((uintptr_t)q % 8 == 0) && (ldq % 8 == 0);
-    const int vec_qT = qT && ((uintptr_t)qT % 16 == 0) && (ldqT % 16 == 0);
     const int nb2 = (int)(ncast < kQuantPass2MaxBlocks ? ncast : kQuantPass2MaxBlocks);
     hipLaunchKernelGGL((quant_pass2_kernel<DT, FMT>), dim3(nb2), dim3(kCastThreads), 0, s, x, rows, cols, ldx,
-                       parts, nparts, used, 1, margin, bias, amax_bits, flags, q, ldq, qT, ldqT, tiles_c, ncast,
-                       vec_in, vec_q, vec_qT);
+                       parts, nparts, used, 1, margin, bias, amax_bits, flags, q, ldq, qT, ldqT, tiles_c, ncast);
 }
 
 template <int DT, int FMT>
@@ -559,12 +570,8 @@ void launch_quantise_delayed_t(const void* x, int64_t rows, int64_t cols, int64_
     int32_t* used = (int32_t*)ws;
     uint32_t* parts = ws + 1;
     if (ntiles > 0) {
-        const int esz = DT == FP8_DT_BF16 ? 2 : 4;
-        const int vec_in = ((uintptr_t)x % 16 == 0) && ((ldx * esz) % 16 == 0);
-        const int vec_q = q && ((uintptr_t)q % 8 == 0) && (ldq % 8 == 0);
-        const int vec_qT = qT && ((uintptr_t)qT % 16 == 0) && (ldqT % 16 == 0);
         hipLaunchKernelGGL((quant_pass1_kernel<DT, FMT, true>), dim3((unsigned)ntiles), dim3(kCastThreads), 0, s, x,
-                           rows, cols, ldx, bias, used, parts, q, ldq, qT, ldqT, tiles_c, vec_in, vec_q, vec_qT);
+                           rows, cols, ldx, bias, used, parts, q, ldq, qT, ldqT, tiles_c);
     }
     hipLaunchKernelGGL((quant_delayed_finish_kernel<DT, FMT>), dim3(1), dim3(kCastThreads), 0, s, parts, (int)ntiles,
                        used, margin, history, hlen, count, bias, amax_bits, flags);
@@ -685,11 +692,10 @@ __global__ void seg_bias_kernel(const uint32_t* __restrict__ amax, const int32_t
 template <int DT, int FMT>
 __global__ __launch_bounds__(kCastThreads) void cast_rows_kernel(
     const void* __restrict__ x, int64_t rows, int64_t cols, int64_t ldx, const int32_t* __restrict__ rowb,
-    uint8_t* __restrict__ q, int64_t ldq, uint8_t* __restrict__ qT, int64_t ldqT, int64_t tiles_c, int vec_in,
-    int vec_q, int vec_qT) {
+    uint8_t* __restrict__ q, int64_t ldq, uint8_t* __restrict__ qT, int64_t ldqT, int64_t tiles_c) {
     __shared__ __attribute__((aligned(16))) uint8_t tile[kCastCols * kCastRows];
     cast_tile<DT, FMT, false, true>(x, rows, cols, ldx, 0, q, ldq, qT, ldqT, blockIdx.x / tiles_c,
-                                    blockIdx.x % tiles_c, vec_in, vec_q, vec_qT, tile, rowb);
+                                    blockIdx.x % tiles_c, tile, rowb);
 }
 
 template <int DT, int FMT>
@@ -709,11 +715,8 @@ void launch_quantise_segments_t(const void* x, int64_t rows, int64_t cols, int64
                        bias, flags, rowb);
     if (rows > 0 && cols > 0 && (q || qT)) {
         const int64_t tiles_r = (rows + kCastRows - 1) / kCastRows, tiles_c = (cols + kCastCols - 1) / kCastCols;
-        const int vec_in = ((uintptr_t)x % 16 == 0) && ((ldx * esz) % 16 == 0);
-        const int vec_q = q && ((uintptr_t)q % 8 == 0) && (ldq % 8 == 0);
-        const int vec_qT = qT && ((uintptr_t)qT % 16 == 0) && (ldqT % 16 == 0);
         hipLaunchKernelGGL((cast_rows_kernel<DT, FMT>), dim3((unsigned)(tiles_r * tiles_c)), dim3(kCastThreads), 0, s,
-                           x, rows, cols, ldx, rowb, q, ldq, qT, ldqT, tiles_c, vec_in, vec_q, vec_qT);
+                           x, rows, cols, ldx, rowb, q, ldq, qT, ldqT, tiles_c);
     }
 }
 
@@ -768,11 +771,10 @@ int32_t launch_scale_bias(const void* x, int dt, int64_t n, int fmt, int32_t mar
                           uint32_t* amax_bits, uint32_t* flags, uint32_t* partials, hipStream_t s) {
     // n == 0: no partials; the finalize pass sees an amax of 0.
     const int nb = n > 0 ? amax_blocks(n) : 0;
-    const int vec = ((uintptr_t)x % 16 == 0) ? 1 : 0;
     if (nb > 0 && dt == FP8_DT_BF16)
-        hipLaunchKernelGGL(amax_partial_kernel<FP8_DT_BF16>, dim3(nb), dim3(kAmaxThreads), 0, s, x, n, vec, partials);
+        hipLaunchKernelGGL(amax_partial_kernel<FP8_DT_BF16>, dim3(nb), dim3(kAmaxThreads), 0, s, x, n, partials);
     else if (nb > 0)
-        hipLaunchKernelGGL(amax_partial_kernel<FP8_DT_F32>, dim3(nb), dim3(kAmaxThreads), 0, s, x, n, vec, partials);
+        hipLaunchKernelGGL(amax_partial_kernel<FP8_DT_F32>, dim3(nb), dim3(kAmaxThreads), 0, s, x, n, partials);
     with_dt_fmt(dt, fmt, [&](auto D, auto F) {
         hipLaunchKernelGGL((amax_finalize_kernel<decltype(D)::value, decltype(F)::value>), dim3(1), dim3(kAmaxThreads), 0,
                            s, partials, nb, margin, bias, amax_bits, flags);

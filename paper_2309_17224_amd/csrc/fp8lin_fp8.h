@@ -272,12 +272,31 @@ __device__ __forceinline__ uint32_t cast1(const void* x, int64_t idx, int b) {
     return c;
 }
 
+// Vector accesses of global memory at any byte address (gfx950 takes them
+// unaligned; an aligned address costs what it did).
+typedef unsigned int u32x2_any __attribute__((ext_vector_type(2), aligned(1)));
+typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+
 // 16-byte load of input data read once per pass, with the non-temporal hint
 // (streaming reads from HBM run about 7-10 % faster with it).
 __device__ __forceinline__ uint4 ld_stream(const void* p) {
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    const u32x4 v = __builtin_nontemporal_load((const u32x4*)p);
+    const u32x4_any v = __builtin_nontemporal_load((const u32x4_any*)p);
     return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+__device__ __forceinline__ uint4 ld16_any(const void* p) {
+    const u32x4_any v = *(const u32x4_any*)p;
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void st8_any(void* p, uint32_t a, uint32_t b) { *(u32x2_any*)p = u32x2_any{a, b}; }
+__device__ __forceinline__ void st16_any(void* p, uint4 v) { *(u32x4_any*)p = u32x4_any{v.x, v.y, v.z, v.w}; }
+
+// v moved down by sh bits (0 <= sh <= 128), zeros from above.
+__device__ __forceinline__ uint4 shr128(uint4 v, int sh) {
+    const uint64_t lo = v.x | ((uint64_t)v.y << 32), hi = v.z | ((uint64_t)v.w << 32);
+    const uint64_t l = sh == 0 ? lo : sh < 64 ? (lo >> sh) | (hi << (64 - sh)) : sh < 128 ? hi >> (sh - 64) : 0;
+    const uint64_t h = sh < 64 ? hi >> sh : 0;
+    return make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
 }
 
 // Two fp32 -> two bf16 (round to nearest even, v_cvt_pk_bf16_f32) in one word.

@@ -17,11 +17,6 @@ namespace {
 
 constexpr int kRk = 128;  // bytes of k per step
 
-__device__ __forceinline__ uint4 ld16_any(const uint8_t* p) {
-    const u32x4_any v = *(const u32x4_any*)p;
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
-
 // Bytes [k, k + 16) of a row of K bytes, zero from K on; reads only bytes of
 // the row.  With K >= 16 one load ending at the row's end, moved down.
 __device__ __forceinline__ uint4 ld16_tail(const uint8_t* row, int64_t k, int64_t K) {
@@ -33,11 +28,7 @@ __device__ __forceinline__ uint4 ld16_tail(const uint8_t* row, int64_t k, int64_
     }
     const int64_t at = min(k, K - 16);
     const int sh = (int)min(k - at, (int64_t)16) * 8;  // bits to drop
-    const uint4 v = ld16_any(row + at);
-    const uint64_t lo = v.x | ((uint64_t)v.y << 32), hi = v.z | ((uint64_t)v.w << 32);
-    const uint64_t l = sh == 0 ? lo : sh < 64 ? (lo >> sh) | (hi << (64 - sh)) : sh < 128 ? hi >> (sh - 64) : 0;
-    const uint64_t h = sh < 64 ? hi >> sh : 0;
-    return make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
+    return shr128(ld16_any(row + at), sh);
 }
 
 // One BM x BN output tile per workgroup, WT x WT per wave.

@@ -83,14 +83,8 @@ __device__ __forceinline__ void tile_of(int b, int nb, int tiles_m, int tiles_n,
     tn = r / gm;
 }
 
-// Global stores of 8 and 16 bytes at any byte address (gfx950 global memory
-// takes unaligned vector accesses), and the 16-byte store with the
-// non-temporal hint: outputs are not read again by the kernel and should not
-// displace cached operands.
-typedef unsigned int u32x2_any __attribute__((ext_vector_type(2), aligned(1)));
-typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
-__device__ __forceinline__ void st8_any(void* p, uint32_t a, uint32_t b) { *(u32x2_any*)p = u32x2_any{a, b}; }
-__device__ __forceinline__ void st16_any(void* p, uint4 v) { *(u32x4_any*)p = u32x4_any{v.x, v.y, v.z, v.w}; }
+// 16-byte store with the non-temporal hint: outputs are not read again by the
+// kernel and should not displace cached operands.
 __device__ __forceinline__ void st_stream(void* p, uint4 v) {
     __builtin_nontemporal_store(u32x4_any{v.x, v.y, v.z, v.w}, (u32x4_any*)p);
 }

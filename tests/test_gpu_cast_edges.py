@@ -1,0 +1,79 @@
+"""Quantise and cast at the edges of the 128 x 128 tiles and at any alignment.
+
+Rows past the last whole tile and columns past the last group of eight take
+clamped or shifted vector loads, and inputs, codes and transposed codes are
+read and written at whatever byte address their offset and stride give.
+Bar: bit for bit the oracle's amax, bias and codes; nothing written outside
+the codes (guard bytes).  Shapes: rows and columns one off 8 and 128, fewer
+than eight columns, one row; every input also as a strided view that starts
+one element into its storage.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2309_17224_amd import fp8lin as F
+from paper_2309_17224_amd import workloads as wl
+from parity_util import i32, np_bits, u32
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 1), (1, 9), (3, 7), (5, 128), (127, 129), (128, 120), (129, 127), (136, 8), (45, 300), (301, 264), (255, 1001)]
+
+
+def view_of(x, strided):
+    """x on the GPU, dense or as a view one element into rows 3 elements longer."""
+    if not strided:
+        return x.cuda()
+    rows, cols = x.shape
+    buf = torch.full((rows * (cols + 3) + 1,), float("inf"), dtype=x.dtype)
+    v = buf[1:].view(rows, cols + 3)[:, :cols]
+    v.copy_(x)
+    return buf.cuda()[1:].view(rows, cols + 3)[:, :cols]
+
+
+def guarded(rows, cols, pad):
+    """uint8 codes [rows, cols] with row stride cols + pad, one byte into a guarded buffer."""
+    buf = torch.full((rows * (cols + pad) + 2,), 0xA5, dtype=torch.uint8, device="cuda")
+    return buf, buf[1:-1].view(rows, cols + pad)[:, :cols]
+
+
+def guard_kept(buf, rows, cols, pad):
+    b = buf.cpu().numpy()
+    tail = b[1:-1].reshape(rows, cols + pad)[:, cols:]
+    return b[0] == 0xA5 and b[-1] == 0xA5 and bool((tail == 0xA5).all())
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "%dx%d" % s)
+@pytest.mark.parametrize("strided", [False, True], ids=["dense", "strided"])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
+@pytest.mark.parametrize("fmt", [F.E4M3, F.E5M2])
+def test_tile_edges(orc, gpu, shape, strided, dtype, fmt):
+    rows, cols = shape
+    x = (wl.small(rows, cols, 1.0, 7 * rows + cols).float() * 1.37).to(dtype)
+    x[rows - 1, cols - 1] = -11.25              # the amax in the last corner
+    xb = np_bits(x)
+    ob, oa, ofl = orc.scale_bias(xb, fmt)
+    oq, oqT = orc.cast(xb, fmt, ob, transpose=True)
+    xd = view_of(x, strided)
+    pad = 3 if strided else 0
+    for pred in (None, ob, ob - 1):
+        bq, q = guarded(rows, cols, pad)
+        bt, qT = guarded(cols, rows, pad)
+        p = None if pred is None else torch.tensor([pred], dtype=torch.int32, device=gpu)
+        _, _, b, a, fl = F.fp8_quantise(xd, fmt, bias_pred=p, q=q, qT=qT)
+        torch.cuda.synchronize()
+        assert (i32(b), u32(a), u32(fl)) == (ob, oa, ofl), f"prediction {pred}"
+        assert np.array_equal(q.cpu().numpy(), oq) and np.array_equal(qT.cpu().numpy(), oqT), f"prediction {pred}"
+        assert guard_kept(bq, rows, cols, pad) and guard_kept(bt, cols, rows, pad)
+
+
+@pytest.mark.parametrize("n", [1, 7, 2049, 100003])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
+def test_scale_bias_unaligned(orc, gpu, n, dtype):
+    x = wl.small(1, n + 1, 1.0, n).to(dtype)[0]
+    x[0] = float("inf")                          # just before the tensor
+    x[n] = 9.5                                   # its last element
+    b, a, fl = F.fp8_scale_bias(x.cuda()[1:], F.E4M3)
+    torch.cuda.synchronize()
+    assert (i32(b), u32(a), u32(fl)) == orc.scale_bias(np_bits(x[1:]), F.E4M3)
