@@ -14,7 +14,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libfp8lin.so")
-SOURCES = ["fp8lin_api.hip", "fp8lin_amax_cast.hip", "fp8lin_gemm.hip", "fp8lin_gemm_ragged.hip", "fp8lin_decoder.hip"]
+SOURCES = ["fp8lin_api.hip", "fp8lin_amax_cast.hip", "fp8lin_gemm.hip", "fp8lin_gemm_ragged.hip", "fp8lin_gemm_stream.hip",
+           "fp8lin_decoder.hip"]
 # measurement aid beside the library (bench.py --mfma-ceiling), not the method
 PROBE_LIB = os.path.join(PKG, "libfp8probe.so")
 PROBE_SOURCE = "fp8probe.hip"

@@ -42,7 +42,7 @@
 //    XCDs; the remap gives each XCD a contiguous range of tiles, walked in
 //    groups of 8 tile-rows, so tiles sharing operand panels meet in the same
 //    L2.
-// Decode kernel (M <= 32): weight-streaming split-K, see below.
+// Outputs too small for these tiles, decode among them: fp8lin_gemm_stream.hip.
 // K not a multiple of 128, or K >= 2^22: fp8lin_gemm_ragged.hip.
 #include "fp8lin_mm.h"
 
@@ -448,211 +448,6 @@ __global__ __launch_bounds__(kMainThreads) void gemm_nt_256(
                                                                    amax_out, qo, bo, ba_rows);
 }
 
-// ------------------------------------------------------------ decode kernel
-// M <= 32 (token-by-token inference): the product is bound by streaming B
-// (the FP8 weight, N x K bytes) from HBM once.  A workgroup of kDecWaves
-// waves owns NB 16-column blocks; wave w takes a contiguous slice of the K
-// range, reads its operand fragments straight from global memory into
-// registers (three 128-byte k-steps in flight), and the partial sums of the
-// waves are added in LDS in a fixed order, so the result does not depend on
-// timing.
-
-__device__ __forceinline__ v8i ld_frag_g(const uint8_t* p) {
-    const uint4 p0 = *(const uint4*)p;
-    const uint4 p1 = *(const uint4*)(p + 16);
-    return v8i{(int)p0.x, (int)p0.y, (int)p0.z, (int)p0.w, (int)p1.x, (int)p1.y, (int)p1.z, (int)p1.w};
-}
-
-// The same with the non-temporal hint, for the weight stream: each weight
-// byte is read once per call, and keeping it out of the caches leaves them to
-// the activation rows every workgroup shares (+38 % weight bandwidth on the
-// Llama-2-70B decode shapes with cold caches).
-__device__ __forceinline__ v8i ld_frag_stream(const uint8_t* p) {
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    const u32x4 p0 = __builtin_nontemporal_load((const u32x4*)p);
-    const u32x4 p1 = __builtin_nontemporal_load((const u32x4*)(p + 16));
-    return v8i{(int)p0.x, (int)p0.y, (int)p0.z, (int)p0.w, (int)p1.x, (int)p1.y, (int)p1.z, (int)p1.w};
-}
-
-// NB: 16-column blocks per workgroup; kDecWaves: waves splitting the K range.
-template <int FA, int FB, int OUT_DT, bool AMAX, int MB, int NB, int kDecWaves>
-__global__ __launch_bounds__(kDecWaves * 64) void gemm_nt_decode(
-    const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, const int32_t* __restrict__ ba_p,
-    const int32_t* __restrict__ bb_p, void* __restrict__ C, int M, int N, int K,
-    uint32_t* __restrict__ amax_out, int ba_rows) {
-    __shared__ __attribute__((aligned(16))) float red[kDecWaves][MB][NB][64][4];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int n0 = blockIdx.x * NB * 16;
-    const int frow = lane & 15, fg = lane >> 4;
-    // fragment sources: row (lane % 16) of each 16-row block, 32 bytes at
-    // k-offset 32 (lane / 16) of every 128-byte step
-    const uint8_t* pa[MB];
-    const uint8_t* pb[NB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) pa[mb] = A + (int64_t)min(mb * 16 + frow, M - 1) * K + fg * 32;
-#pragma unroll
-    for (int j = 0; j < NB; ++j) pb[j] = B + (int64_t)min(n0 + j * 16 + frow, N - 1) * K + fg * 32;
-    const int nkc = K / kBK;
-    const int c0 = (int)((int64_t)nkc * w / kDecWaves), c1 = (int)((int64_t)nkc * (w + 1) / kDecWaves);
-
-    v4f acc[MB][NB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int j = 0; j < NB; ++j) acc[mb][j] = v4f{0.f, 0.f, 0.f, 0.f};
-
-    // three k-steps in flight
-    v8i xa[3][MB], wb[3][NB];
-    auto load = [&](int slot, int c) {
-        const int64_t k0 = (int64_t)c * kBK;
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) xa[slot][mb] = ld_frag_g(pa[mb] + k0);
-#pragma unroll
-        for (int j = 0; j < NB; ++j) wb[slot][j] = ld_frag_stream(pb[j] + k0);
-    };
-    auto step = [&](int slot) {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int j = 0; j < NB; ++j) acc[mb][j] = mfma16<FB, FA>(wb[slot][j], xa[slot][mb], acc[mb][j]);
-    };
-    if (c0 < c1) load(0, c0);
-    if (c0 + 1 < c1) load(1, c0 + 1);
-    for (int c = c0; c < c1; c += 3) {
-        if (c + 2 < c1) load(2, c + 2);
-        step(0);
-        if (c + 1 < c1) {
-            if (c + 3 < c1) load(0, c + 3);
-            step(1);
-        }
-        if (c + 2 < c1) {
-            if (c + 4 < c1) load(1, c + 4);
-            step(2);
-        }
-    }
-
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int j = 0; j < NB; ++j) *(v4f*)red[w][mb][j][lane] = acc[mb][j];
-    __syncthreads();
-    uint32_t mx = 0;
-    for (int slot = threadIdx.x; slot < MB * NB * 64; slot += kDecWaves * 64) {
-        const int mb = slot / (NB * 64), j = (slot / 64) % NB, l = slot & 63;
-        v4f sum = *(const v4f*)red[0][mb][j][l];
-#pragma unroll
-        for (int ww = 1; ww < kDecWaves; ++ww) sum += *(const v4f*)red[ww][mb][j][l];
-        const int64_t m = mb * 16 + (l & 15);
-        const int64_t n = n0 + j * 16 + (l >> 4) * 4;
-        if (n < N) mx = max(mx, store4<OUT_DT>(C, N, m, n, M, N, sum, row_shift(ba_p, ba_rows, *bb_p, m, M)));
-    }
-    if (AMAX) {
-        mx = wave_max_u32(mx);
-        if (lane == 0) atomicMax(amax_out, canon_amax(mx));
-    }
-}
-
-// Staged decode kernel (M <= 16, K a multiple of 512): the same product with
-// the weight rows streamed through LDS.  A load instruction that feeds an MFMA
-// fragment straight from memory touches 16 weight rows K bytes apart, 64 bytes
-// each; here a workgroup copies its BR weight rows (one contiguous block of
-// memory) and the 16 activation rows 512 bytes of k at a time with
-// global_load_lds_dwordx4, each instruction reading 512-byte runs of two
-// rows, three stages in flight, and the waves read the fragments from LDS.
-// Chunk c of LDS row r (16 bytes) is stored at chunk c ^ (r % 16): the 16
-// lanes of every ds_read_b128 phase (lane bit 5 and the parity of lane bits
-// 2..4 fixed; see the main kernel) then hit 16 distinct bank groups.
-// BR = 64: each wave one 16-row block, all k-steps.  BR = 32: waves w and w + 2
-// share block w % 2, each half of every stage's k-steps, added in a fixed order.
-constexpr int kDlKC = 512, kDlBuf = 3;
-
-template <int FA, int FB, int OUT_DT, bool AMAX, int BR>
-__global__ __launch_bounds__(256) void gemm_nt_decode_lds(
-    const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, const int32_t* __restrict__ ba_p,
-    const int32_t* __restrict__ bb_p, void* __restrict__ C, int M, int N, int K,
-    uint32_t* __restrict__ amax_out, int ba_rows) {
-    constexpr int kRows = BR + 16, kStage = kRows * kDlKC, kCpr = kDlKC / 16;
-    constexpr int kNi = kRows / 2;  // copies per stage, two rows each
-    static_assert(kNi % 4 == 0, "copies split over four waves");
-    constexpr int kNiw = kNi / 4;
-    constexpr int kNbb = BR / 16, kWpb = 4 / kNbb, kKs = kDlKC / 128 / kWpb;
-    __shared__ __attribute__((aligned(1024))) uint8_t sm[kDlBuf * kStage];
-    __shared__ __attribute__((aligned(16))) float red[4][64][4];
-    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n0 = blockIdx.x * BR;
-    // copy t of this wave: LDS rows 2d, 2d + 1 (d = kNiw w + t); rows < BR are
-    // weight rows n0 + r (clamped to N - 1), the rest activation rows (clamped
-    // to M - 1); lane -> row 2d + lane / 32, physical chunk lane % 32
-    uint32_t voff[kNiw];
-#pragma unroll
-    for (int t = 0; t < kNiw; ++t) {
-        const int d = w * kNiw + t, r = 2 * d + (lane >> 5), c = (lane & 31) ^ (r & 15);
-        voff[t] = r < BR ? (uint32_t)((min(n0 + r, N - 1) - n0) * K + c * 16)
-                         : (uint32_t)(min(r - BR, M - 1) * K + c * 16);
-    }
-    const uint8_t* bbase = B + (int64_t)n0 * K;
-    const uint32_t lds0 = lds_addr(sm);
-    auto issue = [&](int st) {
-        const int buf = st % kDlBuf;
-#pragma unroll
-        for (int t = 0; t < kNiw; ++t) {
-            const int d = w * kNiw + t;
-            const uint32_t dst = __builtin_amdgcn_readfirstlane(lds0 + buf * kStage + d * 2 * kDlKC);
-            if (2 * d < BR) lds_dma16_nt(bbase + (int64_t)st * kDlKC, voff[t], dst);
-            else lds_dma16_s(A + (int64_t)st * kDlKC, voff[t], dst);
-        }
-    };
-    const int frow = lane & 15, fg = lane >> 4;
-    const int j = w % kNbb, h = w / kNbb;
-    const int rb = 16 * j + frow, ra = BR + frow;
-    v4f acc = {0.f, 0.f, 0.f, 0.f};
-    const int nst = K / kDlKC;
-#pragma unroll
-    for (int st = 0; st < kDlBuf - 1; ++st)
-        if (st < nst) issue(st);
-    for (int st = 0; st < nst; ++st) {
-        // stage st has landed once only the next stage's copies may be pending
-        if (st + 1 < nst) wait_vmcnt<kNiw>();
-        else wait_vmcnt<0>();
-        ws_barrier();
-        // the buffer of stage st - 1, which every wave has finished reading
-        if (st + kDlBuf - 1 < nst) issue(st + kDlBuf - 1);
-        const uint8_t* sb = sm + (st % kDlBuf) * kStage;
-#pragma unroll
-        for (int q = 0; q < kKs; ++q) {
-            const int c0 = (h * kKs + q) * 8 + 2 * fg;
-            const v8i bf = ld_frag(sb + rb * kDlKC, 16 * (c0 ^ (rb & 15)), 16 * ((c0 + 1) ^ (rb & 15)));
-            const v8i af = ld_frag(sb + ra * kDlKC, 16 * (c0 ^ (ra & 15)), 16 * ((c0 + 1) ^ (ra & 15)));
-            acc = mfma16<FB, FA>(bf, af, acc);
-        }
-    }
-    *(v4f*)red[w][lane] = acc;
-    __syncthreads();
-    uint32_t mx = 0;
-    if (w < kNbb) {
-        v4f sum = *(const v4f*)red[w][lane];
-#pragma unroll
-        for (int hh = 1; hh < kWpb; ++hh) sum += *(const v4f*)red[w + hh * kNbb][lane];
-        const int64_t m = lane & 15, n = n0 + w * 16 + (lane >> 4) * 4;
-        if (n < N) mx = store4<OUT_DT>(C, N, m, n, M, N, sum, row_shift(ba_p, ba_rows, *bb_p, m, M));
-    }
-    if (AMAX) {
-        mx = wave_max_u32(mx);
-        if (lane == 0) atomicMax(amax_out, canon_amax(mx));
-    }
-}
-
-template <int FA, int FB, int OUT_DT, bool AMAX, int MB>
-void launch_decode(const uint8_t* A, const int32_t* ba, const uint8_t* B, const int32_t* bb, void* C,
-                   int M, int N, int K, uint32_t* amax, int ba_rows, hipStream_t s) {
-    // 32 output columns per workgroup of 4 waves, each wave a quarter of the
-    // K range (the best of 1-8 column blocks x 4-16 waves on the Llama-2-70B
-    // decode shapes)
-    const int nblk = (N + 31) / 32;
-    hipLaunchKernelGGL((gemm_nt_decode<FA, FB, OUT_DT, AMAX, MB, 2, 4>), dim3(nblk), dim3(4 * 64), 0, s, A, B, ba,
-                       bb, C, M, N, K, amax, ba_rows);
-}
-
 __global__ void fill_u32_kernel(uint32_t* p, uint32_t v) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *p = v;
 }
@@ -701,24 +496,35 @@ void narrow_split(int tiles_m, int tiles_n, int64_t N, int& ndp, int& tw, int& t
     }
 }
 
-// bo.ws != nullptr only where the 256-row or the ragged kernels run.
+// Whether the product goes to the small-tile kernel (fp8lin_gemm_stream.hip),
+// and its tile there.  The rule estimates the time of gemm_nt_256 (us; fit to
+// the same shapes, within 20 %): 1.5 us per k-step and round of 256-wide
+// tiles, 0.64-0.80 for the round of narrower ones plus 0.23 for a full round,
+// and the weight read once.  The small tiles have to be 10 % ahead, so that an
+// estimate that is off does not cost: 512 x 8192 x 8192 61 against 66 us,
+// 1024 x 768 x 768 6.0 against 9.0, 16 x 57344 x 8192 72 against 89 (decode
+// kernels before), but 1024 x 4096 x 4096 34 against 27.
+bool stream_route(int64_t M, int64_t N, int64_t K, int* mb, int* nb) {
+    const double us = stream_tile(M, N, K, mb, nb);
+    if (M <= 32) return true;
+    const int64_t tiles_m = (M + kBM - 1) / kBM, tiles_n = (N + kBN - 1) / kBN;
+    if (tiles_m * tiles_n > 16 * kRound) return false;
+    int ndp, tw, tn2;
+    narrow_split((int)tiles_m, (int)tiles_n, N, ndp, tw, tn2);
+    const double step = 1.5 * ((tiles_m * ndp + kRound - 1) / kRound) + (tw == 64 ? 0.64 : tw == 128 ? 0.71 : tw == 192 ? 0.8 : 0) +
+                        0.23 * (tw ? (double)(tiles_m * tn2) / kRound : 0);
+    return us < 0.9 * (3.8 + K / kBK * step + 5e-8 * (double)N * K);
+}
+
 template <int FA, int FB, int OUT_DT, bool AMAX>
 void launch_t(const uint8_t* A, const int32_t* ba, const uint8_t* B, const int32_t* bb, void* C,
               int64_t M, int64_t N, int64_t K, uint32_t* amax, const BiasOut& bo, int ba_rows, hipStream_t s) {
-    const bool fast = fast_path(A, B, M, N, K);
-    if (fast && M <= 16 && K % kDlKC == 0) {
-        // 64 weight rows per workgroup unless that leaves fewer than 256
-        // workgroups streaming long rows (measured on the Llama-2-70B shapes)
-        if (N >= 64 * 256 || K <= 8192)
-            hipLaunchKernelGGL((gemm_nt_decode_lds<FA, FB, OUT_DT, AMAX, 64>), dim3((unsigned)((N + 63) / 64)), dim3(256),
-                               0, s, A, B, ba, bb, C, (int)M, (int)N, (int)K, amax, ba_rows);
-        else
-            hipLaunchKernelGGL((gemm_nt_decode_lds<FA, FB, OUT_DT, AMAX, 32>), dim3((unsigned)((N + 31) / 32)), dim3(256),
-                               0, s, A, B, ba, bb, C, (int)M, (int)N, (int)K, amax, ba_rows);
-    } else if (fast && M <= 32) {
-        if (M <= 16) launch_decode<FA, FB, OUT_DT, AMAX, 1>(A, ba, B, bb, C, (int)M, (int)N, (int)K, amax, ba_rows, s);
-        else launch_decode<FA, FB, OUT_DT, AMAX, 2>(A, ba, B, bb, C, (int)M, (int)N, (int)K, amax, ba_rows, s);
-    } else if (fast) {
+    int mb, nb;
+    if (!fast_path(A, B, M, N, K)) {
+        launch_gemm_ragged(FA, FB, MmArgs{A, B, ba, bb, C, M, N, K, OUT_DT, AMAX, amax, bo, ba_rows}, s);
+    } else if (stream_route(M, N, K, &mb, &nb)) {
+        launch_gemm_stream(FA, FB, mb, nb, MmArgs{A, B, ba, bb, C, M, N, K, OUT_DT, AMAX, amax, bo, ba_rows}, s);
+    } else {
         const int tiles_m = (int)((M + kBM - 1) / kBM), tiles_n = (int)((N + kBN - 1) / kBN);
         int ndp, tw, tn2;
         narrow_split(tiles_m, tiles_n, N, ndp, tw, tn2);
@@ -731,8 +537,6 @@ void launch_t(const uint8_t* A, const int32_t* ba, const uint8_t* B, const int32
         else if (tw == 192) FP8LIN_GEMM256(192);
         else FP8LIN_GEMM256(0);
 #undef FP8LIN_GEMM256
-    } else {
-        launch_gemm_ragged(FA, FB, MmArgs{A, B, ba, bb, C, M, N, K, OUT_DT, AMAX, amax, bo, ba_rows}, s);
     }
 }
 
@@ -794,8 +598,9 @@ int32_t launch_gemm_nt_quantise(const uint8_t* A, int fa, const int32_t* ba, con
                                 int32_t margin, const int32_t* pred, int32_t* bias, uint32_t* amax_bits,
                                 uint32_t* flags, uint8_t* y8, int64_t ldy8, uint8_t* y8t, int64_t ldy8t,
                                 uint32_t* ws, hipStream_t s) {
-    const bool fused = pred && fast_path(A, B, M, N, K) && M > 32 && (fa == FP8_E4M3 || fa == FP8_E5M2) &&
-                       fb == FP8_E4M3;
+    int mb, nb;
+    const bool fused = pred && fast_path(A, B, M, N, K) && !stream_route(M, N, K, &mb, &nb) &&
+                       (fa == FP8_E4M3 || fa == FP8_E5M2) && fb == FP8_E4M3;
     if (!fused) {  // matmul, then the quantise of its output (same bits, more passes)
         const int32_t st = launch_gemm_nt(A, fa, ba, B, fb, bb, C, FP8_DT_BF16, M, N, K, nullptr, s);
         if (st != FP8_OK) return st;
@@ -838,21 +643,8 @@ int32_t launch_gemm_nt_bias(const uint8_t* A, int fa, const int32_t* ba, const u
                             const int32_t* bb, void* C, int out_dt, int64_t M, int64_t N, int64_t K, int bfmt,
                             int32_t margin, int32_t* bias, uint32_t* amax_bits, uint32_t* flags, uint32_t* ws,
                             hipStream_t s, int ba_rows) {
-    if (!(fast_path(A, B, M, N, K) && M <= 32)) {
-        dispatch_fmts(A, fa, ba, B, fb, bb, C, out_dt, M, N, K, true, amax_bits, BiasOut{bias, flags, ws, bfmt, margin},
-                      ba_rows, s);
-        return hip_status();
-    }
-    // decode kernels: amax with atomics into a zeroed word (ws[0]
-    // if no amax output is wanted, zeroed again afterwards), then the bias
-    uint32_t* acc = amax_bits ? amax_bits : ws;
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, acc, 0u);
-    dispatch_fmts(A, fa, ba, B, fb, bb, C, out_dt, M, N, K, true, acc, BiasOut{}, ba_rows, s);
-    int32_t st = hip_status();
-    if (st != FP8_OK) return st;
-    st = launch_bias_from_amax(acc, bfmt, margin, bias, flags, s);
-    if (st != FP8_OK || acc != ws) return st;
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, ws, 0u);
+    dispatch_fmts(A, fa, ba, B, fb, bb, C, out_dt, M, N, K, true, amax_bits, BiasOut{bias, flags, ws, bfmt, margin},
+                  ba_rows, s);
     return hip_status();
 }
 

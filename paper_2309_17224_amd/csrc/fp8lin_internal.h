@@ -108,6 +108,13 @@ struct MmArgs {
 // The kernels for K not a multiple of 128 (or K >= 2^22): fp8lin_gemm_ragged.hip.
 void launch_gemm_ragged(int fa, int fb, const MmArgs& a, hipStream_t s);
 
+// The kernel for outputs that 256 x 256 tiles would leave most of the chip
+// idle on (fp8lin_gemm_stream.hip), with tiles of 16 mb x 16 nb outputs (K a
+// multiple of 128, 16-byte aligned operands).  stream_tile: its best tile and
+// the estimated time in us.
+double stream_tile(int64_t M, int64_t N, int64_t K, int* mb, int* nb);
+void launch_gemm_stream(int fa, int fb, int mb, int nb, const MmArgs& a, hipStream_t s);
+
 // C[m, n] = 2^-(*ba + *bb) * sum_k A[m, k] * B[n, k]; A [M, K] (format fa),
 // B [N, K] (format fb), both dense; C [M, N] dense of type out_dt.  With
 // ba_rows, ba holds one bias per row of A: 2^-(ba[m] + *bb).
