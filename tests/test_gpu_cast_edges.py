@@ -5,7 +5,8 @@ clamped or shifted vector loads, and inputs, codes and transposed codes are
 read and written at whatever byte address their offset and stride give.
 Bar: bit for bit the oracle's amax, bias and codes; nothing written outside
 the codes (guard bytes).  Shapes: rows and columns one off 8 and 128, fewer
-than eight columns, one row; every input also as a strided view that starts
+than eight columns, one row, both sides of the size up to which one launch
+does it all (160 KiB); every input also as a strided view that starts
 one element into its storage.
 """
 import numpy as np
@@ -18,7 +19,8 @@ from parity_util import i32, np_bits, u32
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(1, 1), (1, 9), (3, 7), (5, 128), (127, 129), (128, 120), (129, 127), (136, 8), (45, 300), (301, 264), (255, 1001)]
+SHAPES = [(1, 1), (1, 9), (3, 7), (5, 128), (127, 129), (128, 120), (129, 127), (136, 8), (45, 300), (301, 264), (255, 1001),
+          (20, 4096), (21, 4096), (4099, 8), (9103, 9), (1025, 129), (1001, 1000)]
 
 
 def view_of(x, strided):
