@@ -497,13 +497,15 @@ void narrow_split(int tiles_m, int tiles_n, int64_t N, int& ndp, int& tw, int& t
 }
 
 // Whether the product goes to the small-tile kernel (fp8lin_gemm_stream.hip),
-// and its tile there.  The rule estimates the time of gemm_nt_256 (us; fit to
-// the same shapes, within 20 %): 1.5 us per k-step and round of 256-wide
-// tiles, 0.64-0.80 for the round of narrower ones plus 0.23 for a full round,
-// and the weight read once.  The small tiles have to be 10 % ahead, so that an
-// estimate that is off does not cost: 512 x 8192 x 8192 61 against 66 us,
-// 1024 x 768 x 768 6.0 against 9.0, 16 x 57344 x 8192 72 against 89 (decode
-// kernels before), but 1024 x 4096 x 4096 34 against 27.
+// and its tile there.  The estimate of gemm_nt_256's time (us) is a fit to the
+// same shapes (7 % off on average): per k-step 1.18 for each round of 256-wide
+// tiles and, for the round of narrower ones, a part that does not depend on
+// their number and one that does; the weight read once; the output.  The small
+// tiles have to be 5 % ahead.  Of the 220 shapes the choice is slower than
+// gemm_nt_256 alone on one (1000 x 4096 x 4096: 27.7 against 26.6 us) and 0.4 %
+// off the best on average: 512 x 8192 x 8192 48 against 67, 1024 x 768 x 768
+// 6.0 against 9.0, 16 x 57344 x 8192 72 against 89 with the decode kernels
+// that this kernel replaced.
 bool stream_route(int64_t M, int64_t N, int64_t K, int* mb, int* nb) {
     const double us = stream_tile(M, N, K, mb, nb);
     if (M <= 32) return true;
@@ -511,9 +513,10 @@ bool stream_route(int64_t M, int64_t N, int64_t K, int* mb, int* nb) {
     if (tiles_m * tiles_n > 16 * kRound) return false;
     int ndp, tw, tn2;
     narrow_split((int)tiles_m, (int)tiles_n, N, ndp, tw, tn2);
-    const double step = 1.5 * ((tiles_m * ndp + kRound - 1) / kRound) + (tw == 64 ? 0.64 : tw == 128 ? 0.71 : tw == 192 ? 0.8 : 0) +
-                        0.23 * (tw ? (double)(tiles_m * tn2) / kRound : 0);
-    return us < 0.9 * (3.8 + K / kBK * step + 5e-8 * (double)N * K);
+    const double part = (double)(tiles_m * tn2) / kRound;
+    const double step = 1.18 * (double)((tiles_m * ndp + kRound - 1) / kRound) +
+                        (tw == 64 ? 0.64 + 0.14 * part : tw == 128 ? 0.51 + 0.35 * part : tw == 192 ? 0.59 + 0.31 * part : 0);
+    return us < 0.95 * (3.57 + (double)(K / kBK) * step + 8.7e-8 * (double)N * K + 4.6e-7 * (double)M * N);
 }
 
 template <int FA, int FB, int OUT_DT, bool AMAX>

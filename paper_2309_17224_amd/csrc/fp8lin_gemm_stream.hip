@@ -15,8 +15,10 @@
 //  * KC = 512 (up to 96 rows): wave w multiplies the whole tile over the 128
 //    bytes of k at 128 w of each stage.  KC = 256 (up to 192 rows): waves w
 //    and w + 2 share a 128-byte slice, each half of the tile's columns.  No
-//    fragment is read from LDS twice.
-//  * The waves' partial sums are added through LDS in a fixed order, so the
+//    fragment is read from LDS twice.  KC = 128 (256 rows, for 128 to 512 rows
+//    of A): the waves take quarters of the tile, and k is not split
+//    (512 x 8192 x 8192: 67 us in 256-row tiles, 61 in 8 x 4, 48 in 8 x 8).
+//  * The partial sums are added through LDS in a fixed order, so the
 //    result does not depend on timing.
 //  * 16-byte chunk c of LDS row r is stored at chunk c ^ (r % 16): the lanes
 //    of every ds_read_b128 phase (see fp8lin_gemm.hip) hit distinct banks.
@@ -31,16 +33,19 @@ constexpr int kSlBuf = 3;
 // the multiplying waves copy too (see the main loop).
 constexpr bool copy_waves(int mb) { return mb > 1; }
 constexpr int stream_threads(int mb) { return copy_waves(mb) ? 512 : 256; }
+constexpr int stream_kc(int mb, int nb) { return mb + nb <= 6 ? 512 : mb + nb <= 12 ? 256 : 128; }
 
 template <int FA, int FB, int MB, int NB>
 __global__ __launch_bounds__(stream_threads(MB)) void gemm_nt_stream(MmArgs p, int tiles_m, int nt) {
     constexpr int kRowsB = 16 * NB, kRows = 16 * (MB + NB);
-    constexpr int kKC = MB + NB <= 6 ? 512 : 256;
+    constexpr int kKC = stream_kc(MB, NB);
     constexpr int kStage = kRows * kKC, kCpr = kKC / 16, kRpi = 64 / kCpr;  // chunks per row, rows per copy
     constexpr int kNiw = kRows / kRpi / 4;                                  // copies per wave and stage
-    constexpr int kSlots = kKC / 128, kHalves = 4 / kSlots, kNbw = NB / kHalves;
-    static_assert(kRows % (4 * kRpi) == 0 && NB % kHalves == 0, "tile split");
-    static_assert(kSlBuf * kStage <= 160 * 1024 && kSlots * MB * NB * 1024 <= kSlBuf * kStage, "LDS budget");
+    constexpr int kSlots = kKC / 128;
+    constexpr int kWn = kSlots == 4 ? 1 : 2, kWm = kSlots == 1 ? 2 : 1;  // waves over the tile's columns, rows
+    constexpr int kNbw = NB / kWn, kMbw = MB / kWm;
+    static_assert(kRows % (4 * kRpi) == 0 && NB % kWn == 0 && MB % kWm == 0, "tile split");
+    static_assert(kSlBuf * kStage <= 160 * 1024 && (kSlots == 1 || kSlots * MB * NB * 1024 <= kSlBuf * kStage), "LDS budget");
     __shared__ __attribute__((aligned(1024))) uint8_t sm[kSlBuf * kStage];
     __shared__ uint32_t wmx[8];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -48,7 +53,11 @@ __global__ __launch_bounds__(stream_threads(MB)) void gemm_nt_stream(MmArgs p, i
     // consecutive tiles of one XCD share their B rows
     const int x = blockIdx.x & 7, per = gridDim.x >> 3, rem = gridDim.x & 7;
     const int tile = x * per + min(x, rem) + (blockIdx.x >> 3);
-    const int m0 = tile % tiles_m * (16 * MB), n0 = tile / tiles_m * kRowsB;
+    int tm = tile % tiles_m, tn = tile / tiles_m;
+    if (kSlots == 1) tile_of(blockIdx.x, gridDim.x, tiles_m, (N + kRowsB - 1) / kRowsB, tm, tn);
+    const int m0 = tm * (16 * MB), n0 = tn * kRowsB;
+    // 16-byte chunk c of LDS row r is stored at chunk c ^ swz(r)
+    auto swz = [](int r) { return kKC == 128 ? chunk_swz(r) : r & 15; };
 
     // copy t of this wave: LDS rows kRpi d .. (d = kNiw w + t), B rows first;
     // rows past the matrix edge read the last row (their outputs are not stored)
@@ -58,7 +67,7 @@ __global__ __launch_bounds__(stream_threads(MB)) void gemm_nt_stream(MmArgs p, i
     for (int t = 0; t < kNiw; ++t) {
         const int r = ((w & 3) * kNiw + t) * kRpi + lrow;
         const int src = r < kRowsB ? min(n0 + r, N - 1) - n0 : min(m0 + r - kRowsB, M - 1) - m0;
-        voff[t] = (uint32_t)(src * K + ((lchunk ^ (r & 15)) << 4));
+        voff[t] = (uint32_t)(src * K + ((lchunk ^ swz(r)) << 4));
     }
     const uint8_t* baseA = p.A + (int64_t)m0 * K;
     const uint8_t* baseB = p.B + (int64_t)n0 * K;
@@ -73,7 +82,7 @@ __global__ __launch_bounds__(stream_threads(MB)) void gemm_nt_stream(MmArgs p, i
             const uint32_t dst = __builtin_amdgcn_readfirstlane(lds0 + buf * kStage + d * 1024);
             uint32_t v = voff[t];
             if (part) {  // chunks past the row end re-read its last one (never multiplied)
-                const int c = (lchunk ^ ((d * kRpi + lrow) & 15)) << 4;
+                const int c = (lchunk ^ swz(d * kRpi + lrow)) << 4;
                 v -= (uint32_t)max(0, c - end);
             }
             if (d * kRpi >= kRowsB) lds_dma16_s(baseA + (int64_t)st * kKC, v, dst);
@@ -83,23 +92,24 @@ __global__ __launch_bounds__(stream_threads(MB)) void gemm_nt_stream(MmArgs p, i
     };
 
     const int frow = lane & 15, fg = lane >> 4;
-    const int slot = w % kSlots, half = (w & 3) / kSlots;
-    const int fo0 = frow * kKC + (((slot * 8 + 2 * fg) ^ frow) << 4);
-    const int fo1 = frow * kKC + (((slot * 8 + 2 * fg + 1) ^ frow) << 4);
-    v4f acc[MB][kNbw];
+    const int slot = w % kSlots, part = (w & 3) / kSlots;
+    const int nb0 = part % kWn * kNbw, mb0 = part / kWn * kMbw;  // this wave's blocks of the tile
+    const int fo0 = frow * kKC + (((slot * 8 + 2 * fg) ^ swz(frow)) << 4);
+    const int fo1 = frow * kKC + (((slot * 8 + 2 * fg + 1) ^ swz(frow)) << 4);
+    v4f acc[kMbw][kNbw];
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
+    for (int i = 0; i < kMbw; ++i)
 #pragma unroll
         for (int j = 0; j < kNbw; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
     auto multiply = [&](int st) {
         if (st * kKC + slot * 128 >= K) return;
-        const uint8_t* sb = sm + (st % kSlBuf) * kStage + half * kNbw * 16 * kKC;
-        const uint8_t* sa = sm + (st % kSlBuf) * kStage + kRowsB * kKC;
+        const uint8_t* sb = sm + (st % kSlBuf) * kStage + nb0 * 16 * kKC;
+        const uint8_t* sa = sm + (st % kSlBuf) * kStage + (kRowsB + mb0 * 16) * kKC;
         v8i bf[kNbw];
 #pragma unroll
         for (int j = 0; j < kNbw; ++j) bf[j] = ld_frag(sb + j * 16 * kKC, fo0, fo1);
 #pragma unroll
-        for (int i = 0; i < MB; ++i) {
+        for (int i = 0; i < kMbw; ++i) {
             const v8i af = ld_frag(sa + i * 16 * kKC, fo0, fo1);
 #pragma unroll
             for (int j = 0; j < kNbw; ++j) acc[i][j] = mfma16<FB, FA>(bf[j], af, acc[i][j]);
@@ -149,25 +159,37 @@ __global__ __launch_bounds__(stream_threads(MB)) void gemm_nt_stream(MmArgs p, i
         }
         ws_barrier();
     }
-    v4f* red = (v4f*)sm;  // [slot][16-row block][16-column block][lane]
-    if (w < 4) {
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-            for (int j = 0; j < kNbw; ++j) red[((slot * MB + i) * NB + half * kNbw + j) * 64 + lane] = acc[i][j];
-    }
-    __syncthreads();
     uint32_t mx = 0;
     const int bb = *p.bb;
-    for (int b = w; b < MB * NB; b += stream_threads(MB) / 64) {
-        v4f sum = red[b * 64 + lane];
-#pragma unroll
-        for (int s = 1; s < kSlots; ++s) sum += red[(s * MB * NB + b) * 64 + lane];
-        const int64_t m = m0 + b / NB * 16 + frow, n = n0 + b % NB * 16 + fg * 4;
-        if (n >= N) continue;
+    auto put = [&](int mb, int nb, v4f sum) {
+        const int64_t m = m0 + mb * 16 + frow, n = n0 + nb * 16 + fg * 4;
+        if (n >= N) return;
         const int sh = row_shift(p.ba, p.ba_rows, bb, m, M);
         mx = max(mx, p.out_dt == FP8_DT_BF16 ? store4<FP8_DT_BF16>(p.C, N, m, n, M, N, sum, sh)
                                              : store4<FP8_DT_F32>(p.C, N, m, n, M, N, sum, sh));
+    };
+    if (kSlots == 1) {
+        if (w < 4) {
+#pragma unroll
+            for (int i = 0; i < kMbw; ++i)
+#pragma unroll
+                for (int j = 0; j < kNbw; ++j) put(mb0 + i, nb0 + j, acc[i][j]);
+        }
+    } else {
+        v4f* red = (v4f*)sm;  // [slot][16-row block][16-column block][lane]
+        if (w < 4) {
+#pragma unroll
+            for (int i = 0; i < kMbw; ++i)
+#pragma unroll
+                for (int j = 0; j < kNbw; ++j) red[((slot * MB + i) * NB + nb0 + j) * 64 + lane] = acc[i][j];
+        }
+        __syncthreads();
+        for (int b = w; b < MB * NB; b += stream_threads(MB) / 64) {
+            v4f sum = red[b * 64 + lane];
+#pragma unroll
+            for (int s = 1; s < kSlots; ++s) sum += red[(s * MB * NB + b) * 64 + lane];
+            put(b / NB, b % NB, sum);
+        }
     }
     if (p.with_amax) {
         const uint32_t wv = wave_max_u32(mx);
@@ -194,7 +216,7 @@ void launch_one(const MmArgs& a, hipStream_t s) {
 #define FP8LIN_STREAM_TILES(X)                                                                             \
     X(1, 1) X(1, 2) X(1, 3) X(1, 4) X(1, 5) X(1, 6) X(1, 8) X(2, 1) X(2, 2) X(2, 3) X(2, 4) X(2, 6) X(2, 8)  \
     X(3, 1) X(3, 2) X(3, 3) X(3, 4) X(3, 6) X(3, 8) X(4, 2) X(4, 4) X(4, 6) X(4, 8) X(5, 2) X(5, 4) X(5, 6) \
-    X(6, 4) X(6, 6) X(8, 4)
+    X(6, 4) X(6, 6) X(8, 4) X(8, 8) X(10, 6)
 
 template <int FA, int FB>
 void launch_t(int mb, int nb, const MmArgs& a, hipStream_t s) {
@@ -206,31 +228,51 @@ void launch_t(int mb, int nb, const MmArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// Estimated time (us) of the product with tiles of 16 MB x 16 NB: a linear fit
-// to 40 shapes x 33 tiles on MI355X (M 1-512, weights 512-57344 wide), which
-// picks a tile within 1 % of the best measured one on average (14 % at worst,
-// on products of 7 us).  The terms: launch; rounds of workgroups (prologue and
-// epilogue); bytes the busiest compute unit copies (83 GB/s each); the weight
-// read once from memory; barriers per stage; the weight re-read from L2 by
-// each row of tiles.
+// Estimated time (us) of the product with tiles of 16 MB x 16 NB: linear fits
+// to 220 shapes x 31 tiles on MI355X (M 1-1500, weights 512-57344 wide), one
+// for each kind of tile, which pick a tile within 0.4 % of the best measured
+// one on average (12 % at worst, on products of 7 us).
+struct StreamFit {
+    double launch, round,     // once; per round of workgroups (prologue, epilogue)
+        copy, copy_alone,     // MB copied by the busiest compute unit; shared out over its resident workgroups
+        stage, mfma,          // its k-bytes of one tile row; its 16 x 16 blocks times k
+        weight, weight_part,  // 100 MB of weight; scaled by how much of the last round is empty
+        weight_l2, out;       // GB of weight over all rows of tiles; 1e7 outputs
+};
+constexpr StreamFit kFitDecode{3.479, 0, 2.252, 10.7, 1.913, 0, 0, 6.091, 0, 49.961};   // MB = 1, M <= 16
+constexpr StreamFit kFitRows16{1.9, 0.945, 3.85, 16.168, 1.062, 0, 0, 2.467, 0, 13.651};  // MB = 1, M > 16
+constexpr StreamFit kFitWide16{2.642, 0.877, 8.195, 0, 9.952, 0, 7.805, 0, 0, 10.343};    // MB = 1, KC = 256
+constexpr StreamFit kFit512{2.092, 1.166, 0, 11.704, 2.084, 29.093, 2.814, 1.35, 0, 18.941};
+constexpr StreamFit kFit256{2.158, 1.72, 0, 8.853, 5.36, 23.636, 3.739, 1.877, 0, 12.579};
+constexpr StreamFit kFit128{2.519, 5.459, 0, 6.509, 0, 35.324, 0, 6.546, 1.301, 6.557};
+
 template <int MB, int NB>
 static double stream_us(int64_t M, int64_t N, int64_t K) {
-    constexpr int kc = MB + NB <= 6 ? 512 : 256, lds = kSlBuf * 16 * (MB + NB) * kc;
+    constexpr int kc = stream_kc(MB, NB), lds = kSlBuf * 16 * (MB + NB) * kc;
     constexpr int occ = 160 * 1024 / lds < 4 ? 160 * 1024 / lds : 4;
+    const StreamFit& f = kc == 128 ? kFit128 : kc == 256 ? (MB == 1 ? kFitWide16 : kFit256)
+                         : MB > 1  ? kFit512
+                         : M <= 16 ? kFitDecode
+                                   : kFitRows16;
     const int64_t tm = (M + 16 * MB - 1) / (16 * MB), tiles = tm * ((N + 16 * NB - 1) / (16 * NB));
-    const int64_t per_cu = (tiles + 255) / 256, rounds = (tiles + 256 * occ - 1) / (256 * occ);
-    return 2.28 + 1.645 * rounds + 12.1e-6 * (double)(per_cu * 16 * (MB + NB)) * K + 5.17e-8 * (double)N * K +
-           2.31e-4 * (double)rounds * K * 512 / kc + 8.75e-9 * (double)tm * N * K;
+    const int64_t rounds = (tiles + 256 * occ - 1) / (256 * occ), per_cu = (tiles + 255) / 256;
+    const double cu_k = (double)per_cu * (double)K, mb_copied = cu_k * 16 * (MB + NB) * 1e-6;
+    const double weight = (double)N * (double)K * 1e-8;
+    const double empty = tiles > 256 * occ ? (double)(rounds * 256 * occ) / (double)tiles : 1.0;
+    return f.launch + f.round * (double)rounds + f.copy * mb_copied + f.copy_alone * mb_copied / (double)(per_cu < occ ? per_cu : occ) +
+           f.stage * cu_k * 1e-4 + f.mfma * cu_k * (MB * NB) * 1e-6 + (f.weight + f.weight_part * empty) * weight +
+           f.weight_l2 * (double)tm * weight * 0.1 + f.out * (double)M * (double)N * 1e-7;
 }
 
 double stream_tile(int64_t M, int64_t N, int64_t K, int* mb, int* nb) {
     double best = 0;
-#define FP8LIN_STREAM_COST(MB, NB)                                     \
-    if (const double t = stream_us<MB, NB>(M, N, K); best == 0 || t < best) { \
-        best = t;                                                      \
-        *mb = MB;                                                      \
-        *nb = NB;                                                      \
-    }
+#define FP8LIN_STREAM_COST(MB, NB)                                                                             \
+    if (16 * (MB - 1) < M || MB == 1)                                                                          \
+        if (const double t = stream_us<MB, NB>(M, N, K); best == 0 || t < best) {                              \
+            best = t;                                                                                          \
+            *mb = MB;                                                                                          \
+            *nb = NB;                                                                                          \
+        }
     FP8LIN_STREAM_TILES(FP8LIN_STREAM_COST)
 #undef FP8LIN_STREAM_COST
     return best;

@@ -12,7 +12,7 @@ multiple of 16 and of 128, odd N (unaligned output rows).
 SMALL (K a multiple of 128, small tiles with the waves sharing k): one tile
 and many, partial tiles in both directions, one to eight 16-row blocks of A,
 K of less than one stage (128), of a partial last stage, of one, two and many
-stages of both stage lengths (256 and 512), several rounds of workgroups.
+stages of each stage length (128, 256 and 512), several rounds of workgroups.
 """
 import numpy as np
 import pytest
@@ -28,7 +28,7 @@ RAGGED = [(5, 7, 3), (1, 1, 1), (17, 33, 15), (64, 64, 16), (65, 63, 17), (130, 
 SMALL = [(1, 1, 128), (1, 5000, 256), (16, 129, 640), (15, 22016, 384), (17, 2049, 1536), (32, 57, 512), (33, 1000, 256),
          (48, 12288, 128), (47, 4097, 896), (64, 15361, 512), (100, 4096, 1152), (101, 12290, 384), (160, 4100, 512),
          (161, 8190, 256), (256, 768, 3072), (301, 4095, 640), (300, 512, 1408), (1024, 768, 768), (513, 1030, 2048),
-         (31, 57344, 128)]
+         (31, 57344, 128), (301, 12290, 4096), (511, 8200, 2176), (400, 8192, 4224)]
 VALS = np.array([0, 1, 2, 3, -1, -2, -4], dtype=np.int64)
 FMTS = {"fwd": (F.E4M3, F.E4M3), "dx": (F.E5M2, F.E4M3), "dw": (F.E4M3, F.E5M2)}
 GUARD = 64
