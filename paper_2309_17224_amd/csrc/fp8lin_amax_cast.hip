@@ -118,6 +118,7 @@ __global__ void bias_from_amax_kernel(const uint32_t* __restrict__ amax_bits, in
 // 16-byte (fp32) accesses, 16 lanes covering 256 (512) contiguous bytes.
 constexpr int kCastRows = 128, kCastCols = 128, kCastThreads = 256, kRpt = 8;
 
+
 __device__ __forceinline__ uint32_t byte_of(uint32_t w, int j) { return (w >> (8 * j)) & 0xFFu; }
 
 // One 128 x 128 tile (tile row tr, tile column tc) of the cast with bias b:
@@ -128,7 +129,10 @@ __device__ __forceinline__ uint32_t byte_of(uint32_t w, int j) { return (w >> (8
 // synchronises through the LDS tile), and it leaves the LDS tile free for
 // the next call.
 // With ROWB, row r is cast with its own bias rowb[r] (clamped) instead of b.
-template <int DT, int FMT, bool MAX, bool ROWB = false>
+// EDGE = false: every tile of the tensor is whole (rows and columns multiples
+// of 128); the kernels that stream large tensors are built both ways, since
+// the edge code costs registers and with them 1-2 % of the bandwidth.
+template <int DT, int FMT, bool MAX, bool ROWB = false, bool EDGE = true>
 __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_t rows, int64_t cols,
                                               int64_t ldx, int b, uint8_t* __restrict__ q, int64_t ldq,
                                               uint8_t* __restrict__ qT, int64_t ldqT, int64_t tr,
@@ -156,11 +160,11 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
     // 1531 x 4096 with transposed codes: 25.0 -> 12.9 us; whole tiles as before
     // (4096 x 11008 with both copies 36 us, 5.0 TB/s).
     const int64_t last = rows - 1;
-    const int64_t left = cols - c0;  // columns of the row from c0 on
-    const bool whole = R0 + kCastRows <= rows && C0 + kCastCols <= cols;  // of the tile: uniform
+    const int64_t left = EDGE ? cols - c0 : 8;  // columns of the row from c0 on
+    const bool whole = !EDGE || (R0 + kCastRows <= rows && C0 + kCastCols <= cols);  // of the tile: uniform
     int64_t at = (whole ? r0 : min(r0, last)) * ldx + c0;
     auto next_row = [&](int i) { at += whole || r0 + i < last ? ldx : 0; };
-    if (cols >= 8) {
+    if (!EDGE || cols >= 8) {
         const int drop = whole || left >= 8 ? 0 : left > 0 ? (int)(8 - left) : 8;  // elements moved out
         at -= drop;
         if (DT == FP8_DT_BF16) {
@@ -197,11 +201,26 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
                 }
             }
         } else {
+            // All rows' loads in flight at once pay in the plain cast and in
+            // small tensors, but cost the quantise of whole tiles, which also
+            // folds the maximum, its occupancy (5.05 -> 4.91 TB/s): there the
+            // compiler interleaves.
+            uint4 va[kRpt], vb[kRpt];
+            const int64_t at0 = at;
+            auto load = [&](int i) {
+                const uint32_t* p = (const uint32_t*)x + (whole ? at0 + i * ldx : left > 0 ? at : 0);
+                va[i] = ld_stream(p);
+                vb[i] = ld_stream(p + 4);
+                if (!whole) next_row(i);
+            };
+            if (!MAX || (EDGE && !whole)) {
+#pragma unroll
+                for (int i = 0; i < kRpt; ++i) load(i);
+            }
 #pragma unroll
             for (int i = 0; i < kRpt; ++i) {
-                const uint32_t* p = (const uint32_t*)x + (left > 0 ? at : 0);
-                uint4 a = ld_stream(p), bb = ld_stream(p + 4);
-                next_row(i);
+                if (MAX && whole) load(i);
+                uint4 a = va[i], bb = vb[i];
                 if (drop) {
                     if (drop & 8) a = bb = make_uint4(0u, 0u, 0u, 0u);
                     if (drop & 4) a = bb, bb = make_uint4(0u, 0u, 0u, 0u);
@@ -281,10 +300,10 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
             const int cl = idx >> 3, qq = idx & 7;
             const int64_t c = C0 + cl;
             const int64_t rr = R0 + qq * 16;
-            if (c >= cols || rr >= rows) continue;
+            if (EDGE && (c >= cols || rr >= rows)) continue;
             const uint4 v = *(const uint4*)(tile + cl * kCastRows + (((qq ^ (cl >> 3)) & 7) << 4));
             uint8_t* dst = qT + c * ldqT + rr;
-            if (rr + 16 <= rows) {
+            if (!EDGE || rr + 16 <= rows) {
                 st16_any(dst, v);
             } else {
                 const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
@@ -297,15 +316,15 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
 }
 
 
-template <int DT, int FMT>
+template <int DT, int FMT, bool EDGE>
 __global__ __launch_bounds__(kCastThreads) void cast_kernel(
     const void* __restrict__ x, int64_t rows, int64_t cols, int64_t ldx,
     const int32_t* __restrict__ bias_p, uint8_t* __restrict__ q, int64_t ldq,
     uint8_t* __restrict__ qT, int64_t ldqT, int64_t tiles_c) {
     __shared__ __attribute__((aligned(16))) uint8_t tile[kCastCols * kCastRows];
     const int b = clamp_bias(*bias_p);
-    cast_tile<DT, FMT, false>(x, rows, cols, ldx, b, q, ldq, qT, ldqT, blockIdx.x / tiles_c,
-                              blockIdx.x % tiles_c, tile);
+    cast_tile<DT, FMT, false, false, EDGE>(x, rows, cols, ldx, b, q, ldq, qT, ldqT, blockIdx.x / tiles_c,
+                                           blockIdx.x % tiles_c, tile);
 }
 
 // ------------------------------------------------- quantise: amax + bias + cast
@@ -318,7 +337,7 @@ __global__ __launch_bounds__(kCastThreads) void cast_kernel(
 // (grid-stride) with the exact bias; otherwise the codes of pass 1 are already
 // those of the exact bias and nothing more is written.  parts[] may come from
 // another producer of the same tensor (a matmul epilogue) with its own tiling.
-template <int DT, int FMT, bool CAST>
+template <int DT, int FMT, bool CAST, bool EDGE>
 __global__ __launch_bounds__(kCastThreads) void quant_pass1_kernel(
     const void* __restrict__ x, int64_t rows, int64_t cols, int64_t ldx,
     const int32_t* __restrict__ bias_pred, int32_t* __restrict__ used, uint32_t* __restrict__ parts,
@@ -330,7 +349,7 @@ __global__ __launch_bounds__(kCastThreads) void quant_pass1_kernel(
         b = clamp_bias(*bias_pred);
         if (blockIdx.x == 0 && threadIdx.x == 0) *used = b;
     }
-    const uint32_t m = cast_tile<DT, FMT, true>(x, rows, cols, ldx, b, CAST ? q : nullptr, ldq,
+    const uint32_t m = cast_tile<DT, FMT, true, false, EDGE>(x, rows, cols, ldx, b, CAST ? q : nullptr, ldq,
                                                 CAST ? qT : nullptr, ldqT, blockIdx.x / tiles_c,
                                                 blockIdx.x % tiles_c, tile);
     const uint32_t bm = block_max(m, red);
@@ -499,7 +518,7 @@ __device__ __forceinline__ int batch_slot(const int64_t* start, int n, int64_t b
     return i;
 }
 
-template <int DT, int FMT, bool CAST>
+template <int DT, int FMT, bool CAST, bool EDGE>
 __global__ __launch_bounds__(kCastThreads) void quant_pass1_batch_kernel(QBatch qb) {
     __shared__ __attribute__((aligned(16))) uint8_t tile[kCastCols * kCastRows];
     __shared__ uint32_t red[kCastThreads / 64];
@@ -510,7 +529,7 @@ __global__ __launch_bounds__(kCastThreads) void quant_pass1_batch_kernel(QBatch 
         b = clamp_bias(*qb.pred[i]);
         if (t == 0 && threadIdx.x == 0) *(int32_t*)qb.ws[i] = b;
     }
-    const uint32_t m = cast_tile<DT, FMT, true>(qb.x[i], qb.rows[i], qb.cols[i], qb.ldx[i], b, CAST ? qb.q[i] : nullptr,
+    const uint32_t m = cast_tile<DT, FMT, true, false, EDGE>(qb.x[i], qb.rows[i], qb.cols[i], qb.ldx[i], b, CAST ? qb.q[i] : nullptr,
                                                 qb.ldq[i], CAST ? qb.qT[i] : nullptr, qb.ldqT[i], t / qb.tiles_c[i],
                                                 t % qb.tiles_c[i], tile);
     const uint32_t bm = block_max(m, red);
@@ -530,13 +549,22 @@ __global__ __launch_bounds__(kCastThreads) void quant_pass2_batch_kernel(QBatch 
                               qb.q[i], qb.ldq[i], qb.qT[i], qb.ldqT[i], qb.tiles_c[i], ntiles);
 }
 
+// fn(true_type) when some tile of a rows x cols tensor is partial.
+bool has_edge(int64_t rows, int64_t cols) { return rows % kCastRows != 0 || cols % kCastCols != 0; }
+template <typename Fn>
+void with_edge(bool edge, Fn&& fn) {
+    if (edge) fn(std::true_type{}); else fn(std::false_type{});
+}
+
 template <int DT, int FMT>
 void launch_cast_t(const void* x, int64_t rows, int64_t cols, int64_t ldx, const int32_t* bias,
                    uint8_t* q, int64_t ldq, uint8_t* qT, int64_t ldqT, hipStream_t s) {
     const int64_t tiles_r = (rows + kCastRows - 1) / kCastRows;
     const int64_t tiles_c = (cols + kCastCols - 1) / kCastCols;
-    hipLaunchKernelGGL((cast_kernel<DT, FMT>), dim3((unsigned)(tiles_r * tiles_c)), dim3(kCastThreads), 0,
-                       s, x, rows, cols, ldx, bias, q, ldq, qT, ldqT, tiles_c);
+    with_edge(has_edge(rows, cols), [&](auto E) {
+        hipLaunchKernelGGL((cast_kernel<DT, FMT, decltype(E)::value>), dim3((unsigned)(tiles_r * tiles_c)), dim3(kCastThreads),
+                           0, s, x, rows, cols, ldx, bias, q, ldq, qT, ldqT, tiles_c);
+    });
 }
 
 constexpr int kQuantPass2MaxBlocks = 1024;
@@ -567,12 +595,15 @@ void launch_quantise_t(const void* x, int64_t rows, int64_t cols, int64_t ldx, i
                            qT, ldqT, (int)tiles_c);
         return;
     }
-    if (bias_pred)
-        hipLaunchKernelGGL((quant_pass1_kernel<DT, FMT, true>), dim3((unsigned)ntiles), dim3(kCastThreads), 0, s,
-                           x, rows, cols, ldx, bias_pred, used, parts, q, ldq, qT, ldqT, tiles_c);
-    else
-        hipLaunchKernelGGL((quant_pass1_kernel<DT, FMT, false>), dim3((unsigned)ntiles), dim3(kCastThreads), 0, s,
-                           x, rows, cols, ldx, bias_pred, used, parts, q, ldq, qT, ldqT, tiles_c);
+    with_edge(has_edge(rows, cols), [&](auto E) {
+        constexpr bool kE = decltype(E)::value;
+        if (bias_pred)
+            hipLaunchKernelGGL((quant_pass1_kernel<DT, FMT, true, kE>), dim3((unsigned)ntiles), dim3(kCastThreads), 0, s,
+                               x, rows, cols, ldx, bias_pred, used, parts, q, ldq, qT, ldqT, tiles_c);
+        else
+            hipLaunchKernelGGL((quant_pass1_kernel<DT, FMT, false, kE>), dim3((unsigned)ntiles), dim3(kCastThreads), 0, s,
+                               x, rows, cols, ldx, bias_pred, used, parts, q, ldq, qT, ldqT, tiles_c);
+    });
     const int nb2 = (int)(ntiles < kQuantPass2MaxBlocks ? ntiles : kQuantPass2MaxBlocks);
     hipLaunchKernelGGL((quant_pass2_kernel<DT, FMT>), dim3(nb2), dim3(kCastThreads), 0, s, x, rows, cols, ldx,
                        parts, (int)ntiles, used, bias_pred ? 1 : 0, margin, bias, amax_bits, flags, q, ldq,
@@ -583,8 +614,9 @@ template <int DT, int FMT>
 void launch_quantise_batch_t(int n, const QuantDesc* d, int32_t margin, hipStream_t s) {
     QBatch qb{};
     qb.n = n;
-    bool pred = false;
+    bool pred = false, edge = false;
     for (int i = 0; i < n; ++i) {
+        edge = edge || has_edge(d[i].rows, d[i].cols);
         const int64_t tiles_c = (d[i].cols + kCastCols - 1) / kCastCols;
         const int64_t ntiles = ((d[i].rows + kCastRows - 1) / kCastRows) * tiles_c;
         qb.t0[i + 1] = qb.t0[i] + ntiles;
@@ -605,12 +637,15 @@ void launch_quantise_batch_t(int n, const QuantDesc* d, int32_t margin, hipStrea
         qb.ws[i] = d[i].ws;
         pred = d[i].pred != nullptr;
     }
-    if (pred)
-        hipLaunchKernelGGL((quant_pass1_batch_kernel<DT, FMT, true>), dim3((unsigned)qb.t0[n]), dim3(kCastThreads), 0,
-                           s, qb);
-    else
-        hipLaunchKernelGGL((quant_pass1_batch_kernel<DT, FMT, false>), dim3((unsigned)qb.t0[n]), dim3(kCastThreads),
-                           0, s, qb);
+    with_edge(edge, [&](auto E) {
+        constexpr bool kE = decltype(E)::value;
+        if (pred)
+            hipLaunchKernelGGL((quant_pass1_batch_kernel<DT, FMT, true, kE>), dim3((unsigned)qb.t0[n]), dim3(kCastThreads), 0,
+                               s, qb);
+        else
+            hipLaunchKernelGGL((quant_pass1_batch_kernel<DT, FMT, false, kE>), dim3((unsigned)qb.t0[n]),
+                               dim3(kCastThreads), 0, s, qb);
+    });
     hipLaunchKernelGGL((quant_pass2_batch_kernel<DT, FMT>), dim3((unsigned)qb.p0[n]), dim3(kCastThreads), 0, s, qb,
                        margin, pred ? 1 : 0);
 }
@@ -637,8 +672,10 @@ void launch_quantise_delayed_t(const void* x, int64_t rows, int64_t cols, int64_
     int32_t* used = (int32_t*)ws;
     uint32_t* parts = ws + 1;
     if (ntiles > 0) {
-        hipLaunchKernelGGL((quant_pass1_kernel<DT, FMT, true>), dim3((unsigned)ntiles), dim3(kCastThreads), 0, s, x,
-                           rows, cols, ldx, bias, used, parts, q, ldq, qT, ldqT, tiles_c);
+        with_edge(has_edge(rows, cols), [&](auto E) {
+            hipLaunchKernelGGL((quant_pass1_kernel<DT, FMT, true, decltype(E)::value>), dim3((unsigned)ntiles),
+                               dim3(kCastThreads), 0, s, x, rows, cols, ldx, bias, used, parts, q, ldq, qT, ldqT, tiles_c);
+        });
     }
     hipLaunchKernelGGL((quant_delayed_finish_kernel<DT, FMT>), dim3(1), dim3(kCastThreads), 0, s, parts, (int)ntiles,
                        used, margin, history, hlen, count, bias, amax_bits, flags);

@@ -20,7 +20,7 @@ from parity_util import i32, np_bits, u32
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(1, 1), (1, 9), (3, 7), (5, 128), (127, 129), (128, 120), (129, 127), (136, 8), (45, 300), (301, 264), (255, 1001),
-          (20, 4096), (21, 4096), (4099, 8), (9103, 9), (1025, 129), (1001, 1000)]
+          (20, 4096), (21, 4096), (4099, 8), (9103, 9), (1025, 129), (1001, 1000), (384, 256)]
 
 
 def view_of(x, strided):
