@@ -7,9 +7,8 @@ Training (Sec. 2, 2.2, 2.3, 3): three scaling biases per layer and call,
   b_g = bias(dY, E5) - margin   dY8, dY8T = cast_E5(dY * 2^b_g)
   dX  = 2^-(b_g + b_w) dY8 . W8^T
   dW  = 2^-(b_x + b_g) X8^T . dY8
-The forward and grad-input matmuls also return the amax of their outputs
-(epilogue reduction), from which the next consumer's bias is taken without a
-second read of Y or dX (fp8_bias_from_amax).
+The forward and grad-input matmuls also return the amax of their outputs and
+the next consumer's bias in the same launch, without a second read of Y or dX.
 
 Inference (Sec. 3.1): W8T and b_w come once from ptq_quantise_weights; each
 call computes b_x and X8, then the forward matmul.
@@ -43,6 +42,7 @@ class LinearBuffers:
     dw: torch.Tensor
     scal: torch.Tensor      # int32 [16]: biases, amax bits, flags
     ws: torch.Tensor
+    bws: torch.Tensor | None = None  # zeros between calls: in-launch biases of y and dx
 
     # views into scal
     @property
@@ -92,30 +92,38 @@ def alloc(M: int, K: int, N: int, device, y_dtype=torch.bfloat16, dx_dtype=torch
         dx=e((M, K), dtype=dx_dtype, device=device) if train else e((0, 0), dtype=dx_dtype, device=device),
         dw=e((K, N), dtype=dw_dtype, device=device) if train else e((0, 0), dtype=dw_dtype, device=device),
         scal=torch.zeros(16, dtype=torch.int32, device=device),
-        ws=F.workspace(nmax, device),
+        ws=torch.empty(max(F.fp8_scale_bias_ws_bytes(nmax), *(F.fp8_quantise_ws_bytes(r, c) for r, c in ((M, K), (K, N), (M, N))), 4),
+                       dtype=torch.uint8, device=device),
+        bws=F.bias_workspace(device),
     )
+
+
+def _quantise(x: torch.Tensor, fmt: int, margin: int, bias, amax, flags, q, qT, ws) -> None:
+    """amax, bias and cast of a contiguous tensor in one call: the codes of
+    fp8_scale_bias followed by the cast, in one launch fewer (two fewer for
+    small tensors)."""
+    if not x.is_contiguous():
+        raise ValueError("the linear layer needs contiguous tensors")
+    F.fp8_quantise(x, fmt, margin, bias=bias, amax_bits=amax, flags=flags, q=q, qT=qT, want_qT=qT is not None, ws=ws)
 
 
 def quantise_weight(w: torch.Tensor, b: LinearBuffers) -> None:
     """bias + cast of the weight: after every weight update (Sec. 3.2), or
     once at checkpoint load (Sec. 3.1)."""
-    F.fp8_scale_bias(w, F.E4M3, 0, bias=b.bw, amax_bits=b.amax_w, flags=b.flags_w, ws=b.ws)
-    F.fp8_cast_e4(w, b.bw, q=b.w8, qT=b.w8t)
+    _quantise(w, F.E4M3, 0, b.bw, b.amax_w, b.flags_w, b.w8, b.w8t, b.ws)
 
 
 def forward(x: torch.Tensor, b: LinearBuffers, keep_xt: bool = True) -> torch.Tensor:
-    F.fp8_scale_bias(x, F.E4M3, 0, bias=b.bx, amax_bits=b.amax_x, flags=b.flags_x, ws=b.ws)
-    F.fp8_cast_e4(x, b.bx, q=b.x8, qT=b.x8t if keep_xt else None, want_qT=keep_xt)
-    F.fp8_linear_fwd(b.x8, b.bx, b.w8t, b.bw, y=b.y, y_amax_bits=b.amax_y)
-    F.fp8_bias_from_amax(b.amax_y, F.E4M3, 0, bias=b.by, flags=b.flags_y)
+    _quantise(x, F.E4M3, 0, b.bx, b.amax_x, b.flags_x, b.x8, b.x8t if keep_xt else None, b.ws)
+    F.fp8_linear_fwd_bias(b.x8, b.bx, b.w8t, b.bw, F.E4M3, 0, y=b.y, bias=b.by, amax_bits=b.amax_y, flags=b.flags_y,
+                          ws=b.bws)
     return b.y
 
 
 def backward(dy: torch.Tensor, b: LinearBuffers, margin: int = 0):
-    F.fp8_scale_bias(dy, F.E5M2, margin, bias=b.bg, amax_bits=b.amax_g, flags=b.flags_g, ws=b.ws)
-    F.fp8_cast_e5(dy, b.bg, q=b.dy8, qT=b.dy8t)
-    F.fp8_linear_bwd_dx(b.dy8, b.bg, b.w8, b.bw, dx=b.dx, dx_amax_bits=b.amax_dx)
-    F.fp8_bias_from_amax(b.amax_dx, F.E5M2, margin, bias=b.bdx, flags=b.flags_dx)
+    _quantise(dy, F.E5M2, margin, b.bg, b.amax_g, b.flags_g, b.dy8, b.dy8t, b.ws)
+    F.fp8_linear_bwd_dx_bias(b.dy8, b.bg, b.w8, b.bw, F.E5M2, margin, dx=b.dx, bias=b.bdx, amax_bits=b.amax_dx,
+                             flags=b.flags_dx, ws=b.bws)
     F.fp8_linear_bwd_dw(b.x8t, b.bx, b.dy8t, b.bg, dw=b.dw)
     return b.dx, b.dw
 
@@ -132,8 +140,7 @@ def train_step(x: torch.Tensor, w: torch.Tensor, dy: torch.Tensor, b: LinearBuff
 def infer_step(x: torch.Tensor, b: LinearBuffers) -> torch.Tensor:
     """PTQ inference call: activation bias + cast, then the forward matmul
     with the weight quantised beforehand (quantise_weight / ptq)."""
-    F.fp8_scale_bias(x, F.E4M3, 0, bias=b.bx, amax_bits=b.amax_x, flags=b.flags_x, ws=b.ws)
-    F.fp8_cast_e4(x, b.bx, q=b.x8)
+    _quantise(x, F.E4M3, 0, b.bx, b.amax_x, b.flags_x, b.x8, None, b.ws)
     F.fp8_linear_fwd(b.x8, b.bx, b.w8t, b.bw, y=b.y)
     return b.y
 
