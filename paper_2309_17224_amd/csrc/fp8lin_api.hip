@@ -576,3 +576,46 @@ int32_t llama_residual_add(const void* a, const void* b, void* out, int64_t n, v
 }
 
 }  // extern "C"
+
+// ---- for the tests and measurements: not declared in fp8lin.h, not part of the ABI
+extern "C" {
+
+// Kernel (MmKernel) that a matmul of these sizes takes, and its tile in
+// 16-row blocks of A and of B for the small-tile kernel (0 otherwise).
+int32_t fp8lin_mm_route(int64_t M, int64_t N, int64_t K, int32_t* mb, int32_t* nb) {
+    const MmRoute r = mm_route(M, N, K);
+    *mb = r.mb;
+    *nb = r.nb;
+    return r.kernel;
+}
+
+// Tile i of the small-tile kernel; 0 past the last one.
+int32_t fp8lin_mm_tile(int32_t i, int32_t* mb, int32_t* nb) { return stream_tile_at(i, mb, nb) ? 1 : 0; }
+
+// fp8_linear_fwd (fa = FP8_E4M3), fp8_linear_bwd_dx (FP8_E5M2) or, with fb =
+// FP8_E5M2, fp8_linear_bwd_dw through a given kernel and tile.  With ws,
+// as the entry points with an in-launch bias; otherwise amax may be null.
+int32_t fp8lin_mm_forced(int32_t kernel, int32_t mb, int32_t nb, const uint8_t* a, int32_t fa, const int32_t* ba,
+                         const uint8_t* b, int32_t fb, const int32_t* bb, void* c, int32_t c_dt, int64_t M, int64_t N,
+                         int64_t K, int32_t fmt, int32_t margin, int32_t* bias, uint32_t* amax, uint32_t* flags,
+                         void* ws, size_t ws_bytes, void* stream) {
+    const bool fmts = (fa == FP8_E4M3 && (fb == FP8_E4M3 || fb == FP8_E5M2)) || (fa == FP8_E5M2 && fb == FP8_E4M3);
+    if (!fmts || !dt_ok(c_dt) || M < 1 || N < 1 || K < 0 || M > INT32_MAX || N > INT32_MAX) return FP8_EINVAL;
+    if (!a || !b || !ba || !bb || !c || !a16(a) || !a16(b) || !aligned(c, esize(c_dt))) return FP8_EINVAL;
+    const MmRoute r{kernel, mb, nb};
+    if (kernel == kMmStream) {
+        bool built = false;
+        for (int i = 0, tm, tn; !built && stream_tile_at(i, &tm, &tn); ++i) built = tm == mb && tn == nb;
+        if (!built) return FP8_EINVAL;
+    } else if (kernel != kMmRagged && kernel != kMm256) {
+        return FP8_EINVAL;
+    }
+    if (kernel != kMmRagged && (K % 128 != 0 || K >= (1 << 22))) return FP8_EINVAL;
+    if (!ws)
+        return launch_gemm_nt(a, fa, ba, b, fb, bb, c, c_dt, M, N, K, amax, as_stream(stream), 0, &r);
+    if (!fmt_ok(fmt) || !bias || !aligned(ws, 4) || ws_bytes < fp8_linear_bias_ws_bytes()) return FP8_EINVAL;
+    return launch_gemm_nt_bias(a, fa, ba, b, fb, bb, c, c_dt, M, N, K, fmt, margin, bias, amax, flags, (uint32_t*)ws,
+                               as_stream(stream), 0, &r);
+}
+
+}  // extern "C"

@@ -452,13 +452,6 @@ __global__ void fill_u32_kernel(uint32_t* p, uint32_t v) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *p = v;
 }
 
-// The LDS-staged kernels need K a multiple of 128, 16-byte aligned operands
-// and 32-bit offsets within a tile.
-bool fast_path(const uint8_t* A, const uint8_t* B, int64_t M, int64_t N, int64_t K) {
-    return (K % kBK == 0) && ((uintptr_t)A % 16 == 0) && ((uintptr_t)B % 16 == 0) && M <= INT32_MAX &&
-           N <= INT32_MAX && K < (1 << 22);
-}
-
 // Workgroups of the 256-row kernel that run at once (one per CU of gfx950).
 constexpr int kRound = 256;
 
@@ -520,13 +513,12 @@ bool stream_route(int64_t M, int64_t N, int64_t K, int* mb, int* nb) {
 }
 
 template <int FA, int FB, int OUT_DT, bool AMAX>
-void launch_t(const uint8_t* A, const int32_t* ba, const uint8_t* B, const int32_t* bb, void* C,
+void launch_t(const MmRoute& r, const uint8_t* A, const int32_t* ba, const uint8_t* B, const int32_t* bb, void* C,
               int64_t M, int64_t N, int64_t K, uint32_t* amax, const BiasOut& bo, int ba_rows, hipStream_t s) {
-    int mb, nb;
-    if (!fast_path(A, B, M, N, K)) {
+    if (r.kernel == kMmRagged) {
         launch_gemm_ragged(FA, FB, MmArgs{A, B, ba, bb, C, M, N, K, OUT_DT, AMAX, amax, bo, ba_rows}, s);
-    } else if (stream_route(M, N, K, &mb, &nb)) {
-        launch_gemm_stream(FA, FB, mb, nb, MmArgs{A, B, ba, bb, C, M, N, K, OUT_DT, AMAX, amax, bo, ba_rows}, s);
+    } else if (r.kernel == kMmStream) {
+        launch_gemm_stream(FA, FB, r.mb, r.nb, MmArgs{A, B, ba, bb, C, M, N, K, OUT_DT, AMAX, amax, bo, ba_rows}, s);
     } else {
         const int tiles_m = (int)((M + kBM - 1) / kBM), tiles_n = (int)((N + kBN - 1) / kBN);
         int ndp, tw, tn2;
@@ -545,27 +537,27 @@ void launch_t(const uint8_t* A, const int32_t* ba, const uint8_t* B, const int32
 
 // with_amax: epilogue amax (into *amax, or folded into bo.ws).
 template <int FA, int FB>
-void dispatch_out(const uint8_t* A, const int32_t* ba, const uint8_t* B, const int32_t* bb, void* C,
+void dispatch_out(const MmRoute& r, const uint8_t* A, const int32_t* ba, const uint8_t* B, const int32_t* bb, void* C,
                   int out_dt, int64_t M, int64_t N, int64_t K, bool with_amax, uint32_t* amax,
                   const BiasOut& bo, int ba_rows, hipStream_t s) {
     if (out_dt == FP8_DT_BF16) {
-        if (with_amax) launch_t<FA, FB, FP8_DT_BF16, true>(A, ba, B, bb, C, M, N, K, amax, bo, ba_rows, s);
-        else launch_t<FA, FB, FP8_DT_BF16, false>(A, ba, B, bb, C, M, N, K, amax, bo, ba_rows, s);
+        if (with_amax) launch_t<FA, FB, FP8_DT_BF16, true>(r, A, ba, B, bb, C, M, N, K, amax, bo, ba_rows, s);
+        else launch_t<FA, FB, FP8_DT_BF16, false>(r, A, ba, B, bb, C, M, N, K, amax, bo, ba_rows, s);
     } else {
-        if (with_amax) launch_t<FA, FB, FP8_DT_F32, true>(A, ba, B, bb, C, M, N, K, amax, bo, ba_rows, s);
-        else launch_t<FA, FB, FP8_DT_F32, false>(A, ba, B, bb, C, M, N, K, amax, bo, ba_rows, s);
+        if (with_amax) launch_t<FA, FB, FP8_DT_F32, true>(r, A, ba, B, bb, C, M, N, K, amax, bo, ba_rows, s);
+        else launch_t<FA, FB, FP8_DT_F32, false>(r, A, ba, B, bb, C, M, N, K, amax, bo, ba_rows, s);
     }
 }
 
-void dispatch_fmts(const uint8_t* A, int fa, const int32_t* ba, const uint8_t* B, int fb, const int32_t* bb,
+void dispatch_fmts(const MmRoute& r, const uint8_t* A, int fa, const int32_t* ba, const uint8_t* B, int fb, const int32_t* bb,
                    void* C, int out_dt, int64_t M, int64_t N, int64_t K, bool with_amax, uint32_t* amax,
                    const BiasOut& bo, int ba_rows, hipStream_t s) {
     if (fa == FP8_E4M3 && fb == FP8_E4M3)
-        dispatch_out<FP8_E4M3, FP8_E4M3>(A, ba, B, bb, C, out_dt, M, N, K, with_amax, amax, bo, ba_rows, s);
+        dispatch_out<FP8_E4M3, FP8_E4M3>(r, A, ba, B, bb, C, out_dt, M, N, K, with_amax, amax, bo, ba_rows, s);
     else if (fa == FP8_E5M2 && fb == FP8_E4M3)
-        dispatch_out<FP8_E5M2, FP8_E4M3>(A, ba, B, bb, C, out_dt, M, N, K, with_amax, amax, bo, ba_rows, s);
+        dispatch_out<FP8_E5M2, FP8_E4M3>(r, A, ba, B, bb, C, out_dt, M, N, K, with_amax, amax, bo, ba_rows, s);
     else  // the ABI's products: E4 x E4, E5 x E4, E4 x E5
-        dispatch_out<FP8_E4M3, FP8_E5M2>(A, ba, B, bb, C, out_dt, M, N, K, with_amax, amax, bo, ba_rows, s);
+        dispatch_out<FP8_E4M3, FP8_E5M2>(r, A, ba, B, bb, C, out_dt, M, N, K, with_amax, amax, bo, ba_rows, s);
 }
 
 template <int FA, int FB, int QF>
@@ -590,6 +582,15 @@ void fused_fmt(int qfmt, const uint8_t* A, const int32_t* ba, const uint8_t* B, 
 
 }  // namespace
 
+// The LDS-staged kernels need K a multiple of 128 and 32-bit offsets within a
+// tile.
+MmRoute mm_route(int64_t M, int64_t N, int64_t K) {
+    if (K % kBK != 0 || K >= (1 << 22)) return {kMmRagged, 0, 0};
+    int mb, nb;
+    if (stream_route(M, N, K, &mb, &nb)) return {kMmStream, mb, nb};
+    return {kMm256, 0, 0};
+}
+
 int64_t gemm_quantise_ws_words(int64_t M, int64_t N) {
     const int64_t tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
     const int64_t q = quantise_ws_words(M, N);
@@ -601,11 +602,10 @@ int32_t launch_gemm_nt_quantise(const uint8_t* A, int fa, const int32_t* ba, con
                                 int32_t margin, const int32_t* pred, int32_t* bias, uint32_t* amax_bits,
                                 uint32_t* flags, uint8_t* y8, int64_t ldy8, uint8_t* y8t, int64_t ldy8t,
                                 uint32_t* ws, hipStream_t s) {
-    int mb, nb;
-    const bool fused = pred && fast_path(A, B, M, N, K) && !stream_route(M, N, K, &mb, &nb) &&
-                       (fa == FP8_E4M3 || fa == FP8_E5M2) && fb == FP8_E4M3;
+    const MmRoute route = mm_route(M, N, K);
+    const bool fused = pred && route.kernel == kMm256 && (fa == FP8_E4M3 || fa == FP8_E5M2) && fb == FP8_E4M3;
     if (!fused) {  // matmul, then the quantise of its output (same bits, more passes)
-        const int32_t st = launch_gemm_nt(A, fa, ba, B, fb, bb, C, FP8_DT_BF16, M, N, K, nullptr, s);
+        const int32_t st = launch_gemm_nt(A, fa, ba, B, fb, bb, C, FP8_DT_BF16, M, N, K, nullptr, s, 0, &route);
         if (st != FP8_OK) return st;
         return launch_quantise(C, FP8_DT_BF16, M, N, N, qfmt, margin, pred, bias, amax_bits, flags, y8, ldy8, y8t,
                                ldy8t, ws, s);
@@ -636,18 +636,19 @@ int32_t launch_fill_u32(uint32_t* p, uint32_t v, hipStream_t s) {
 
 int32_t launch_gemm_nt(const uint8_t* A, int fa, const int32_t* ba, const uint8_t* B, int fb,
                        const int32_t* bb, void* C, int out_dt, int64_t M, int64_t N, int64_t K,
-                       uint32_t* amax_bits, hipStream_t s, int ba_rows) {
+                       uint32_t* amax_bits, hipStream_t s, int ba_rows, const MmRoute* route) {
     if (amax_bits) hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, amax_bits, 0u);
-    dispatch_fmts(A, fa, ba, B, fb, bb, C, out_dt, M, N, K, amax_bits != nullptr, amax_bits, BiasOut{}, ba_rows, s);
+    dispatch_fmts(route ? *route : mm_route(M, N, K), A, fa, ba, B, fb, bb, C, out_dt, M, N, K, amax_bits != nullptr,
+                  amax_bits, BiasOut{}, ba_rows, s);
     return hip_status();
 }
 
 int32_t launch_gemm_nt_bias(const uint8_t* A, int fa, const int32_t* ba, const uint8_t* B, int fb,
                             const int32_t* bb, void* C, int out_dt, int64_t M, int64_t N, int64_t K, int bfmt,
                             int32_t margin, int32_t* bias, uint32_t* amax_bits, uint32_t* flags, uint32_t* ws,
-                            hipStream_t s, int ba_rows) {
-    dispatch_fmts(A, fa, ba, B, fb, bb, C, out_dt, M, N, K, true, amax_bits, BiasOut{bias, flags, ws, bfmt, margin},
-                  ba_rows, s);
+                            hipStream_t s, int ba_rows, const MmRoute* route) {
+    dispatch_fmts(route ? *route : mm_route(M, N, K), A, fa, ba, B, fb, bb, C, out_dt, M, N, K, true, amax_bits,
+                  BiasOut{bias, flags, ws, bfmt, margin}, ba_rows, s);
     return hip_status();
 }
 

@@ -278,6 +278,16 @@ double stream_tile(int64_t M, int64_t N, int64_t K, int* mb, int* nb) {
     return best;
 }
 
+bool stream_tile_at(int i, int* mb, int* nb) {
+#define FP8LIN_STREAM_ENTRY(MB, NB) {MB, NB},
+    static constexpr int tiles[][2] = {FP8LIN_STREAM_TILES(FP8LIN_STREAM_ENTRY)};
+#undef FP8LIN_STREAM_ENTRY
+    if (i < 0 || i >= (int)(sizeof(tiles) / sizeof(tiles[0]))) return false;
+    *mb = tiles[i][0];
+    *nb = tiles[i][1];
+    return true;
+}
+
 void launch_gemm_stream(int fa, int fb, int mb, int nb, const MmArgs& a, hipStream_t s) {
     if (fa == FP8_E4M3 && fb == FP8_E4M3) launch_t<FP8_E4M3, FP8_E4M3>(mb, nb, a, s);
     else if (fa == FP8_E5M2 && fb == FP8_E4M3) launch_t<FP8_E5M2, FP8_E4M3>(mb, nb, a, s);

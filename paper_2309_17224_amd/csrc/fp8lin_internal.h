@@ -111,16 +111,27 @@ void launch_gemm_ragged(int fa, int fb, const MmArgs& a, hipStream_t s);
 // The kernel for outputs that 256 x 256 tiles would leave most of the chip
 // idle on (fp8lin_gemm_stream.hip), with tiles of 16 mb x 16 nb outputs (K a
 // multiple of 128, 16-byte aligned operands).  stream_tile: its best tile and
-// the estimated time in us.
+// the estimated time in us.  stream_tile_at: the tiles the kernel is built
+// for, i = 0, 1, ...; false past the last one.
 double stream_tile(int64_t M, int64_t N, int64_t K, int* mb, int* nb);
+bool stream_tile_at(int i, int* mb, int* nb);
 void launch_gemm_stream(int fa, int fb, int mb, int nb, const MmArgs& a, hipStream_t s);
 
+// Which kernel a matmul takes, and its tile in 16-row blocks if it is the
+// small-tile kernel: a function of the sizes alone.
+enum MmKernel { kMmRagged = 0, kMmStream = 1, kMm256 = 2 };
+struct MmRoute {
+    int kernel, mb, nb;
+};
+MmRoute mm_route(int64_t M, int64_t N, int64_t K);
+
 // C[m, n] = 2^-(*ba + *bb) * sum_k A[m, k] * B[n, k]; A [M, K] (format fa),
-// B [N, K] (format fb), both dense; C [M, N] dense of type out_dt.  With
-// ba_rows, ba holds one bias per row of A: 2^-(ba[m] + *bb).
+// B [N, K] (format fb), both dense and, if K > 0, starting on 16-byte
+// boundaries; C [M, N] dense of type out_dt.  With ba_rows, ba holds one bias
+// per row of A: 2^-(ba[m] + *bb).  route: null, mm_route's.
 int32_t launch_gemm_nt(const uint8_t* A, int fa, const int32_t* ba, const uint8_t* B, int fb,
                        const int32_t* bb, void* C, int out_dt, int64_t M, int64_t N, int64_t K,
-                       uint32_t* amax_bits, hipStream_t s, int ba_rows = 0);
+                       uint32_t* amax_bits, hipStream_t s, int ba_rows = 0, const MmRoute* route = nullptr);
 
 // Per row segment of x (rows offsets[s] .. offsets[s+1]-1): amax, Eq. 3 bias
 // and flags into [nseg] arrays, the bias of every row into row_bias [rows],
@@ -141,7 +152,7 @@ int32_t launch_bias_mode(const int32_t* bias, int64_t n, int32_t* ring, int64_t 
 int32_t launch_gemm_nt_bias(const uint8_t* A, int fa, const int32_t* ba, const uint8_t* B, int fb,
                             const int32_t* bb, void* C, int out_dt, int64_t M, int64_t N, int64_t K, int bfmt,
                             int32_t margin, int32_t* bias, uint32_t* amax_bits, uint32_t* flags, uint32_t* ws,
-                            hipStream_t s, int ba_rows = 0);
+                            hipStream_t s, int ba_rows = 0, const MmRoute* route = nullptr);
 
 // ---- decoder-layer glue (fp8lin_decoder.hip)
 // The FP8-AMAX quantise fused into a glue kernel's bf16 output: codes cast

@@ -4,8 +4,8 @@ running maximum into amax, bias and flags).
 
 Bar: bit-exact against the unfused calls (the matmul with its epilogue amax,
 then fp8_bias_from_amax), for every format and margin, bf16 and fp32 outputs,
-shapes that take the 256 x 256 kernel and shapes that fall back (M <= 32, K
-not a multiple of 128); the workspace must be zero after every call.  Where
+shapes that take the 256 x 256 kernel, the small tiles and the kernel for K
+not a multiple of 128; the workspace must be zero after every call.  Where
 the product is exact (small integer codes), the oracle's product and bias are
 the reference.
 """
@@ -15,13 +15,16 @@ import numpy as np
 import pytest
 import torch
 
+import mm_routes as R
 from paper_2309_17224_amd import fp8lin as F
 from parity_util import i32, np_bits, u32
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(256, 256, 128), (300, 520, 384), (1024, 768, 768), (2048, 4096, 1024),  # 256 x 256 kernel
-          (16, 1024, 256), (130, 200, 100)]                                          # fallbacks
+MAIN = [(2048, 4096, 1024), (700, 4099, 128), (1030, 2305, 256)]
+SMALL = [(256, 256, 128), (300, 520, 384), (1024, 768, 768), (16, 1024, 256)]
+SHAPES = MAIN + SMALL + [(130, 200, 100)]
+MAIN_DX = [(4096, 1024, 2048), (1030, 256, 2305)]  # dX [M, K] over N
 FMTS = [F.E4M3, F.E5M2, F.E4_A, F.E5_A]
 
 
@@ -45,6 +48,13 @@ def bits(t):
     return t.view(torch.int16) if t.dtype == torch.bfloat16 else t.view(torch.int32)
 
 
+def test_routes():
+    """The shapes take the kernels they are listed for."""
+    assert [R.kernel(*s) for s in MAIN] == [R.MAIN] * len(MAIN)
+    assert [R.kernel(*s) for s in SMALL] == [R.STREAM] * len(SMALL)
+    assert [R.kernel(m, k, n) for m, n, k in MAIN_DX] == [R.MAIN] * len(MAIN_DX)
+
+
 @pytest.mark.parametrize("shape", SHAPES, ids=str)
 @pytest.mark.parametrize("fmt", FMTS)
 @pytest.mark.parametrize("out_dt", [F.DT_BF16, F.DT_F32])
@@ -61,7 +71,7 @@ def test_fwd_bias_matches_unfused(gpu, shape, fmt, out_dt):
         assert not ws.any(), "workspace not left zero"
 
 
-@pytest.mark.parametrize("shape", [(512, 384, 640), (40, 256, 128), (1000, 300, 260), (4096, 1024, 2048)], ids=str)
+@pytest.mark.parametrize("shape", MAIN_DX + [(512, 384, 640), (40, 256, 128), (1000, 300, 260)], ids=str)
 @pytest.mark.parametrize("fmt", [F.E5M2, F.E5_A])
 def test_dx_bias_matches_unfused(gpu, shape, fmt):
     M, N, K = shape  # dX [M, K] = dY8 [M, N] . W8 [K, N]^T
@@ -101,8 +111,7 @@ def test_workspace_reuse_across_calls_and_shapes(gpu):
 
 @pytest.mark.parametrize("shape", [(512, 512, 256), (16, 256, 128), (100, 64, 100)], ids=str)
 def test_null_amax_and_flags(gpu, shape):
-    """The C entry point with no amax or flags output (the fallback kernels
-    then use the workspace as their atomic target and clear it again)."""
+    """The C entry point with no amax or flags output."""
     M, N, K = shape
     x8, bx, w8t, bw = operands(gpu, M, N, K, 9)
     y0, b0, _, _ = unfused_fwd(x8, bx, w8t, bw, F.E5M2, 1, F.DT_BF16)
@@ -120,9 +129,9 @@ def test_null_amax_and_flags(gpu, shape):
 
 def test_special_outputs(gpu):
     """All-zero product (bias 0, FLAG_ZERO) and a NaN code in X (NaN row of Y,
-    FLAG_NONFINITE), on the 256 x 256 kernel and on a fallback."""
+    FLAG_NONFINITE), on the 256 x 256 kernel and on small tiles."""
     ws = F.bias_workspace(gpu)
-    for M, N, K in ((512, 512, 256), (20, 256, 128)):
+    for M, N, K in ((1030, 2305, 256), (512, 512, 256), (20, 256, 128)):
         x8 = torch.zeros(M, K, dtype=torch.uint8, device=gpu)
         w8t = torch.full((N, K), 0x38, dtype=torch.uint8, device=gpu)
         z = torch.zeros(1, dtype=torch.int32, device=gpu)

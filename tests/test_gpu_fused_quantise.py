@@ -5,21 +5,26 @@ codes) of the bf16 output, for the next layer.
 Bar: bit-exact against the unfused calls (the matmul, then fp8_quantise on
 its output, itself bit-exact against the oracle), for predictions that hold,
 miss, are absent or alias the bias word, in every FP8 format, on shapes that
-take the fused 256x256 kernel and on shapes that fall back (M <= 32, K not a
-multiple of 128).  Where the product is exact (small integer codes), the
-oracle's own product, quantised by the oracle, is the reference.
+take the fused 256 x 256 kernel (whole tiles, and partial ones with odd rows
+and columns) and on shapes that do not (small tiles, K not a multiple of 128),
+where the matmul and the quantise are separate launches.  Where the product is
+exact (small integer codes), the oracle's own product, quantised by the
+oracle, is the reference.
 """
 import numpy as np
 import pytest
 import torch
 
+import mm_routes as R
 from paper_2309_17224_amd import fp8lin as F
 from parity_util import i32, np_bits, u32
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(256, 256, 128), (300, 520, 384), (1024, 768, 768), (2048, 4096, 1024),  # fused
-          (16, 1024, 256), (130, 200, 100)]                                          # fallback
+FUSED = [(2048, 4096, 1024), (700, 4099, 128), (1030, 2305, 256), (2049, 1100, 128)]
+SEPARATE = [(256, 256, 128), (300, 520, 384), (1024, 768, 768), (16, 1024, 256), (130, 200, 100)]
+SHAPES = FUSED + SEPARATE
+FUSED_DX = [(1030, 256, 2305), (513, 384, 5001)]  # dX [M, K] over N
 PREDS = [None, 0, 1, -3, "alias"]
 
 
@@ -48,6 +53,13 @@ def pred_tensors(gpu, pred, exact):
     return torch.tensor([exact + pred], dtype=torch.int32, device=gpu), bias
 
 
+def test_routes():
+    """The shapes take the kernels they are listed for."""
+    assert [R.kernel(*s) for s in FUSED] == [R.MAIN] * len(FUSED)
+    assert all(R.kernel(*s) != R.MAIN for s in SEPARATE)
+    assert [R.kernel(m, k, n) for m, n, k in FUSED_DX] == [R.MAIN] * len(FUSED_DX)
+
+
 @pytest.mark.parametrize("shape", SHAPES, ids=str)
 @pytest.mark.parametrize("pred", PREDS, ids=str)
 @pytest.mark.parametrize("fmt", [F.E4M3, F.E5M2, F.E4_A, F.E5_A])
@@ -66,7 +78,7 @@ def test_fwd_fused_quantise_matches_unfused(gpu, shape, pred, fmt):
     assert torch.equal(qT, qT0), "transposed codes differ"
 
 
-@pytest.mark.parametrize("shape", [(512, 384, 640), (40, 256, 128), (1000, 300, 260)], ids=str)
+@pytest.mark.parametrize("shape", FUSED_DX + [(512, 384, 640), (40, 256, 128), (1000, 300, 260)], ids=str)
 @pytest.mark.parametrize("pred", [None, 0, 2], ids=str)
 def test_dx_fused_quantise_matches_unfused(gpu, shape, pred):
     M, N, K = shape  # dX [M, K] = dY8 [M, N] . W8 [K, N]^T
@@ -87,11 +99,12 @@ def test_dx_fused_quantise_matches_unfused(gpu, shape, pred):
     assert torch.equal(q, q0) and torch.equal(qT, qT0)
 
 
-def test_fused_quantise_against_oracle_on_exact_products(orc, gpu):
+@pytest.mark.parametrize("shape", [(384, 512, 256), (700, 4099, 128)], ids=str)
+def test_fused_quantise_against_oracle_on_exact_products(orc, gpu, shape):
     """Codes from {0, +-1, +-2, +-3, +-4, +-6, +-8} with K < 2^14 give exact
     fp32 sums, so the oracle's product is the GPU's, and the oracle's bias and
     cast of it are the reference for the fused epilogue."""
-    M, N, K = 384, 512, 256
+    M, N, K = shape
     vals = np.array([0x00, 0x38, 0x40, 0x44, 0x48, 0x4C, 0x50], dtype=np.uint8)  # E4M3 0,1,2,3,4,6,8
     rng = np.random.default_rng(5)
     def codes(r, c):

@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 import torch
 
+import mm_routes as R
 from paper_2309_17224_amd import fp8lin as F
 from parity_util import REL_F_TOL, i32, np_bits, rel_f, u32
 
@@ -150,18 +151,21 @@ def test_epilogue_amax(orc, gpu, out_dt):
     assert amax_dx == oa2
 
 
-# Shapes of the 256 x 256 kernel (with and without a narrow last round), the
-# decode kernels and the byte-load kernel (K not a multiple of 128).
-NAN_SHAPES = [(300, 520, 256), (512, 700, 384), (16, 640, 512), (24, 100, 256), (40, 90, 200)]
+# Shapes of the 256 x 256 kernel (its last round 64 and 192 columns wide, and
+# none narrower), the small tiles and the kernel for K not a multiple of 128.
+NAN_SHAPES = [(R.MAIN, (1030, 2305, 256)), (R.MAIN, (257, 16390, 128)), (R.MAIN, (4100, 4200, 128)),
+              (R.STREAM, (300, 520, 256)), (R.STREAM, (512, 700, 384)), (R.STREAM, (16, 640, 512)),
+              (R.STREAM, (24, 100, 256)), (R.RAGGED, (40, 90, 200))]
 
 
-@pytest.mark.parametrize("shape", NAN_SHAPES, ids=lambda s: "%dx%dx%d" % s)
+@pytest.mark.parametrize("kernel,shape", NAN_SHAPES, ids=lambda s: "%dx%dx%d" % s if isinstance(s, tuple) else str(s))
 @pytest.mark.parametrize("out_dt", [F.DT_BF16, F.DT_F32], ids=["bf16", "f32"])
-def test_epilogue_amax_of_nan_output_is_canonical(orc, gpu, shape, out_dt):
+def test_epilogue_amax_of_nan_output_is_canonical(orc, gpu, kernel, shape, out_dt):
     """A NaN code in an operand makes outputs NaN; their amax, through the
     epilogue atomics and through the in-launch bias, is 0x7FC00000 with
     FP8_FLAG_NONFINITE and bias 0, the oracle's amax of a tensor holding NaN."""
     M, N, K = shape
+    assert R.kernel(M, N, K) == kernel
     rng = np.random.default_rng(M + N + K)
     A = rand_codes((M, K), 0, rng, orc)
     B = rand_codes((N, K), 0, rng, orc)
@@ -210,10 +214,9 @@ def test_gemm_deterministic(orc, gpu):
     assert torch.equal(y1, y2)
 
 
-# Decode shapes (M <= 32 routes to the weight-streaming kernels; 33 does not).
-# M <= 16 with K a multiple of 512 takes the LDS-staged kernel: 64 weight rows
-# per workgroup (K <= 8192 or N >= 16384) or 32; one stage (K = 512), exactly
-# as many stages as buffers (1536), long K with few workgroups, ragged N.
+# Decode shapes: all take the small-tile kernel, whose stages hold 512 or 256
+# bytes of k: less than one stage (K = 128), one (512), as many as it has
+# buffers (1536), a partial last one, long K with few workgroups, ragged N.
 DECODE = [(1, 64, 128), (2, 1000, 1024), (15, 65, 896), (16, 4096, 8192), (17, 130, 384),
           (31, 192, 2048), (32, 1, 128), (33, 100, 256), (16, 63, 28672), (1, 130, 512),
           (7, 33, 1536), (16, 200, 9216), (12, 16390, 512)]

@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 import torch
 
+import mm_routes as R
 from paper_2309_17224_amd import fp8lin as F
 from parity_util import i32, np_bits, u32
 
@@ -83,14 +84,18 @@ def test_special_values_per_segment(orc, gpu):
     assert np.array_equal(q.cpu().numpy(), oq) and np.array_equal(qT.cpu().numpy(), oqT)
 
 
-@pytest.mark.parametrize("shape", [(300, 520, 384), (16, 1024, 256), (20, 512, 256), (100, 64, 100),
-                                   (2048, 1024, 512), (12, 1000, 1024), (9, 96, 10240)], ids=str)
+@pytest.mark.parametrize("shape", [(R.MAIN, (2048, 4096, 512)), (R.MAIN, (1030, 2305, 256)), (R.STREAM, (300, 520, 384)),
+                                   (R.STREAM, (16, 1024, 256)), (R.STREAM, (20, 512, 256)), (R.RAGGED, (100, 64, 100)),
+                                   (R.STREAM, (12, 1000, 1024)), (R.STREAM, (9, 96, 10240)),
+                                   (R.MAIN, (2048, 1024, 512))], ids=str)
 def test_fwd_rows_is_the_product_unscaled_per_row(gpu, shape):
     """Y of the per-row matmul is the same kernel's fp32 product S (taken with
     zero biases), unscaled row by row: Y[m] = round(S[m] * 2^-(rb[m] + bw)),
-    on the 256 x 256, decode (both staged row counts and the fragment-loading
-    kernel) and fallback kernels; and its epilogue amax."""
+    on the 256 x 256 and small tiles and the kernel for K not a multiple of
+    128; and its epilogue amax."""
+    kernel, shape = shape
     M, N, K = shape
+    assert R.kernel(M, N, K) == kernel
     x = data(M, K, M + K, F.DT_BF16).to(gpu)
     g = torch.Generator().manual_seed(N)
     w = (torch.randn(N, K, generator=g) * 0.02).to(torch.bfloat16).to(gpu)

@@ -2,11 +2,12 @@
 outputs in the matmul launches) against the separate calls they stand for
 (fp8_scale_bias, fp8_cast_e4 / e5, the matmuls with the epilogue amax,
 fp8_bias_from_amax): every code, bias, amax, flag and output, bit for bit,
-on sizes that take each matmul kernel, with and without a margin, twice (the
+on sizes whose matmuls take each kernel, with and without a margin, twice (the
 workspaces are reused)."""
 import pytest
 import torch
 
+import mm_routes as R
 from paper_2309_17224_amd import fp8lin as F
 from paper_2309_17224_amd import linear as L
 from paper_2309_17224_amd import workloads as wl
@@ -18,7 +19,17 @@ def bits(t):
     return t.view(torch.int16) if t.dtype == torch.bfloat16 else t.view(torch.int32) if t.dtype == torch.float32 else t
 
 
-@pytest.mark.parametrize("size", [(1024, 768, 768), (255, 264, 136), (48, 512, 640), (16, 128, 384), (1, 8, 8)], ids=str)
+SIZES = [(1024, 768, 768), (255, 264, 136), (48, 512, 640), (16, 128, 384), (1, 8, 8), (1152, 2432, 2304)]
+
+
+def test_routes():
+    """Forward, grad-input and grad-weight products each take each kernel at
+    one of the sizes."""
+    for product in (lambda m, k, n: (m, n, k), lambda m, k, n: (m, k, n), lambda m, k, n: (k, n, m)):
+        assert {R.kernel(*product(*s)) for s in SIZES} == {R.RAGGED, R.STREAM, R.MAIN}
+
+
+@pytest.mark.parametrize("size", SIZES, ids=str)
 @pytest.mark.parametrize("margin", [0, 3])
 def test_step_is_the_separate_calls(gpu, size, margin):
     M, K, N = size
