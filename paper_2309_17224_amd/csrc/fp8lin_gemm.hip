@@ -44,6 +44,8 @@
 //    L2.
 // Outputs too small for these tiles, decode among them: fp8lin_gemm_stream.hip.
 // K not a multiple of 128, or K >= 2^22: fp8lin_gemm_ragged.hip.
+#include <algorithm>
+
 #include "fp8lin_mm.h"
 
 namespace fp8lin {
@@ -489,27 +491,23 @@ void narrow_split(int tiles_m, int tiles_n, int64_t N, int& ndp, int& tw, int& t
     }
 }
 
-// Whether the product goes to the small-tile kernel (fp8lin_gemm_stream.hip),
-// and its tile there.  The estimate of gemm_nt_256's time (us) is a fit to the
-// same shapes (7 % off on average): per k-step 1.18 for each round of 256-wide
-// tiles and, for the round of narrower ones, a part that does not depend on
-// their number and one that does; the weight read once; the output.  The small
-// tiles have to be 5 % ahead.  Of the 220 shapes the choice is slower than
-// gemm_nt_256 alone on one (1000 x 4096 x 4096: 27.7 against 26.6 us) and 0.4 %
-// off the best on average: 512 x 8192 x 8192 48 against 67, 1024 x 768 x 768
-// 6.0 against 9.0, 16 x 57344 x 8192 72 against 89 with the decode kernels
-// that this kernel replaced.
-bool stream_route(int64_t M, int64_t N, int64_t K, int* mb, int* nb) {
-    const double us = stream_tile(M, N, K, mb, nb);
-    if (M <= 32) return true;
+// Estimated time (us) of gemm_nt_256: a fit to its times at 33 to 2048 rows
+// and weights 512 to 57344 wide, on codes of normal data, weights in cache and
+// not (4 % off on average).  Per k-step: a part for each round of 256-wide
+// tiles; for the round of narrower ones, a part that does not depend on their
+// number and one that does; a part that grows as the operand panels of one XCD
+// (up to 8 tile rows of A, its eighth of B) outgrow its 4 MB of L2.  Then the
+// weight read once, and the output.
+double main_us(int64_t M, int64_t N, int64_t K) {
     const int64_t tiles_m = (M + kBM - 1) / kBM, tiles_n = (N + kBN - 1) / kBN;
-    if (tiles_m * tiles_n > 16 * kRound) return false;
     int ndp, tw, tn2;
     narrow_split((int)tiles_m, (int)tiles_n, N, ndp, tw, tn2);
     const double part = (double)(tiles_m * tn2) / kRound;
-    const double step = 1.18 * (double)((tiles_m * ndp + kRound - 1) / kRound) +
-                        (tw == 64 ? 0.64 + 0.14 * part : tw == 128 ? 0.51 + 0.35 * part : tw == 192 ? 0.59 + 0.31 * part : 0);
-    return us < 0.95 * (3.57 + (double)(K / kBK) * step + 8.7e-8 * (double)N * K + 4.6e-7 * (double)M * N);
+    const double weight = (double)N * (double)K, panels = (double)std::min<int64_t>(M, 8 * kBM) * (double)K + weight / 8;
+    const double step = 1.24 * (double)((tiles_m * ndp + kRound - 1) / kRound) +
+                        (tw == 64 ? 0.479 + 0.026 * part : tw == 128 ? 0.129 + 0.489 * part : tw == 192 ? 0.171 + 0.564 * part : 0) +
+                        0.142 * std::min(1.0, std::max(0.0, (panels * 1e-6 - 3) / 3));
+    return 4.554 + (double)(K / kBK) * step + 4.93e-8 * weight + 2.193e-7 * (double)M * (double)N;
 }
 
 template <int FA, int FB, int OUT_DT, bool AMAX>
@@ -583,11 +581,20 @@ void fused_fmt(int qfmt, const uint8_t* A, const int32_t* ba, const uint8_t* B, 
 }  // namespace
 
 // The LDS-staged kernels need K a multiple of 128 and 32-bit offsets within a
-// tile.
+// tile.  The small tiles (fp8lin_gemm_stream.hip) take up to 32 rows always,
+// and beyond that where they are estimated to be faster: of 700 measured
+// products of 33 to 2048 rows the choice is slower than gemm_nt_256 on five,
+// by 1 to 4 % but for 160 x 15360 x 5120 (36.3 against 32.7 us), and 0.6 % off
+// the best on average: 512 x 8192 x 8192 45.5 against 48.3 us, 1024 x 768 x 768
+// 6.0 against 7.8, 64 x 4096 x 11008 16.8 against 55.8; 1024 x 4096 x 4096 27.8
+// against 26.4 and 100 x 22016 x 4096 32.8 against 26.1, so those go there.
 MmRoute mm_route(int64_t M, int64_t N, int64_t K) {
     if (K % kBK != 0 || K >= (1 << 22)) return {kMmRagged, 0, 0};
-    int mb, nb;
-    if (stream_route(M, N, K, &mb, &nb)) return {kMmStream, mb, nb};
+    MmRoute r{kMmStream, 0, 0};
+    const double us = stream_tile(M, N, K, &r.mb, &r.nb);
+    if (M <= 32) return r;
+    const int64_t tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
+    if (tiles <= 16 * kRound && us < main_us(M, N, K)) return r;
     return {kMm256, 0, 0};
 }
 

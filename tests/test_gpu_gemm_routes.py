@@ -33,8 +33,9 @@ RAGGED = [(5, 7, 3), (1, 1, 1), (17, 33, 15), (64, 64, 16), (65, 63, 17), (130, 
           (300, 257, 1000), (2304, 4101, 255), (4100, 2050, 144), (2049, 2049, 15)]
 SMALL = [(1, 1, 128), (1, 5000, 256), (16, 129, 640), (15, 22016, 384), (17, 2049, 1536), (32, 57, 512), (33, 1000, 256),
          (47, 4097, 896), (64, 15361, 512), (100, 4096, 1152), (160, 4100, 512), (256, 768, 3072), (301, 4095, 640),
-         (300, 512, 1408), (1024, 768, 768), (513, 1030, 2048), (31, 57344, 128), (400, 8192, 4224)]
-MAIN = [(101, 12290, 384), (161, 8190, 256), (301, 12290, 4096), (511, 8200, 2176), (700, 4099, 128), (1030, 2305, 256)]
+         (300, 512, 1408), (1024, 768, 768), (513, 1030, 2048), (31, 57344, 128), (513, 4100, 5248)]
+MAIN = [(101, 12290, 384), (161, 8190, 256), (301, 12290, 4096), (511, 8200, 2176), (700, 4099, 128), (1030, 2305, 256),
+        (400, 8192, 4224)]
 SHAPES = [(R.RAGGED, s) for s in RAGGED] + [(R.STREAM, s) for s in SMALL] + [(R.MAIN, s) for s in MAIN]
 VALS = np.array([0, 1, 2, 3, -1, -2, -4], dtype=np.int64)
 FMTS = {"fwd": (F.E4M3, F.E4M3), "dx": (F.E5M2, F.E4M3), "dw": (F.E4M3, F.E5M2)}

@@ -1,0 +1,28 @@
+"""Which kernel a matmul takes (no GPU needed): the rule is a function of the
+sizes, evaluated on the host."""
+import pytest
+
+import mm_routes as R
+
+# Products timed on MI355X in the small tiles and in the 256 x 256 kernel (us).
+SLOWER_IN_SMALL_TILES = {(717, 2304, 768): (8.6, 8.1), (555, 4096, 4096): (26.4, 25.3), (768, 4096, 4096): (26.9, 25.6),
+                         (1024, 4096, 4096): (27.8, 26.4), (256, 12288, 4096): (28.3, 27.6), (100, 22016, 4096): (33.8, 30.7),
+                         (768, 2816, 1024): (10.3, 9.2), (450, 8192, 4096): (28.0, 26.2), (256, 11008, 4096): (26.9, 25.5)}
+FASTER_IN_SMALL_TILES = {(33, 768, 768): (3.4, 6.8), (64, 4096, 11008): (16.8, 55.8), (301, 4096, 4096): (15.6, 20.9),
+                         (512, 8192, 8192): (45.5, 48.3), (1024, 768, 768): (6.0, 7.8), (1024, 512, 512): (4.6, 6.6),
+                         (1000, 4096, 11008): (57.0, 67.1), (512, 1024, 8192): (17.5, 46.1)}
+
+
+@pytest.mark.parametrize("shape", SLOWER_IN_SMALL_TILES, ids=str)
+def test_products_slower_in_small_tiles_take_large_ones(shape):
+    assert R.kernel(*shape) == R.MAIN
+
+
+@pytest.mark.parametrize("shape", FASTER_IN_SMALL_TILES, ids=str)
+def test_products_faster_in_small_tiles_take_them(shape):
+    assert R.kernel(*shape) == R.STREAM
+
+
+def test_rows_of_a_decode_and_odd_contractions():
+    assert all(R.kernel(m, n, 4096) == R.STREAM for m in (1, 16, 32) for n in (64, 4096, 57344))
+    assert all(R.kernel(512, 4096, k) == R.RAGGED for k in (1, 127, 4032, 4097, 1 << 22))
