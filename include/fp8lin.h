@@ -360,10 +360,12 @@ int32_t fp8_linear_bwd_dx(const uint8_t *dy8, const int32_t *bg, const uint8_t *
 /*
  * fp8_linear_fwd_bias / fp8_linear_bwd_dx_bias -- fp8_linear_fwd /
  * fp8_linear_bwd_dx with the amax of the output turned into the Eq. 3 bias
- * (Sec. 3) for the layer that consumes it, in the same launch: the same
+ * (Sec. 3) for the layer that consumes it, in the same call: the same
  * y / dx, bias, amax and flags as the matmul with y_amax_bits followed by
- * fp8_bias_from_amax, without the separate zeroing and bias launches (the
- * last workgroup of the matmul to finish computes the bias).
+ * fp8_bias_from_amax, without the separate zeroing launch, and without the
+ * bias launch (the last workgroup of the matmul to finish computes the bias)
+ * but for outputs of more than 64 small tiles, whose workgroups all finish at
+ * once: there one thread computes it in a launch after the matmul.
  * y / dx:  out, as fp8_linear_fwd / fp8_linear_bwd_dx (bf16 or fp32).
  * *_fmt, margin: format and margin of the bias (as fp8_scale_bias).
  * *_bias:  out, the bias.  *_amax_bits, *_flags: out, optional (NULL).

@@ -580,10 +580,11 @@ int32_t llama_residual_add(const void* a, const void* b, void* out, int64_t n, v
 // ---- for the tests and measurements: not declared in fp8lin.h, not part of the ABI
 extern "C" {
 
-// Kernel (MmKernel) that a matmul of these sizes takes, and its tile in
-// 16-row blocks of A and of B for the small-tile kernel (0 otherwise).
-int32_t fp8lin_mm_route(int64_t M, int64_t N, int64_t K, int32_t* mb, int32_t* nb) {
-    const MmRoute r = mm_route(M, N, K);
+// Kernel (MmKernel) that a matmul of these sizes takes, with or without an
+// amax or bias of its output, and its tile in 16-row blocks of A and of B for
+// the small-tile kernel (0 otherwise).
+int32_t fp8lin_mm_route(int64_t M, int64_t N, int64_t K, int32_t with_amax, int32_t* mb, int32_t* nb) {
+    const MmRoute r = mm_route(M, N, K, with_amax != 0);
     *mb = r.mb;
     *nb = r.nb;
     return r.kernel;

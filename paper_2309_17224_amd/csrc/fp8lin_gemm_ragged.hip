@@ -182,23 +182,27 @@ __global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_nt_ragged(MmA
     }
 }
 
+// Tiles of 256 x 128 from 128 of them on, else of 64 x 64.
+bool big_tiles(int64_t M, int64_t N) { return ((M + 255) / 256) * ((N + 127) / 128) >= 128; }
+
+template <int FA, int FB, int BM, int BN, int WT>
+void launch_tiles(const MmArgs& a, hipStream_t s) {
+    const int tm = (int)((a.M + BM - 1) / BM), tn = (int)((a.N + BN - 1) / BN);
+    hipLaunchKernelGGL((gemm_nt_ragged<FA, FB, BM, BN, WT>), dim3((unsigned)(tm * tn)), dim3((BM / WT) * (BN / WT) * 64), 0, s,
+                       a, tm, tn);
+}
+
 template <int FA, int FB>
 void launch_t(const MmArgs& a, hipStream_t s) {
-    auto tiles = [&](int bm, int bn, int& tm, int& tn) {
-        tm = (int)((a.M + bm - 1) / bm);
-        tn = (int)((a.N + bn - 1) / bn);
-        return (int64_t)tm * tn;
-    };
-    int tm, tn;
-    if (tiles(256, 128, tm, tn) >= 128) {
-        hipLaunchKernelGGL((gemm_nt_ragged<FA, FB, 256, 128, 64>), dim3((unsigned)(tm * tn)), dim3(512), 0, s, a, tm, tn);
-    } else {
-        tiles(64, 64, tm, tn);
-        hipLaunchKernelGGL((gemm_nt_ragged<FA, FB, 64, 64, 32>), dim3((unsigned)(tm * tn)), dim3(256), 0, s, a, tm, tn);
-    }
+    if (big_tiles(a.M, a.N)) launch_tiles<FA, FB, 256, 128, 64>(a, s);
+    else launch_tiles<FA, FB, 64, 64, 32>(a, s);
 }
 
 }  // namespace
+
+int64_t ragged_workgroups(int64_t M, int64_t N) {
+    return big_tiles(M, N) ? ((M + 255) / 256) * ((N + 127) / 128) : ((M + 63) / 64) * ((N + 63) / 64);
+}
 
 void launch_gemm_ragged(int fa, int fb, const MmArgs& a, hipStream_t s) {
     if (fa == FP8_E4M3 && fb == FP8_E4M3) launch_t<FP8_E4M3, FP8_E4M3>(a, s);

@@ -106,24 +106,27 @@ struct MmArgs {
 };
 
 // The kernels for K not a multiple of 128 (or K >= 2^22): fp8lin_gemm_ragged.hip.
+int64_t ragged_workgroups(int64_t M, int64_t N);
 void launch_gemm_ragged(int fa, int fb, const MmArgs& a, hipStream_t s);
 
 // The kernel for outputs that 256 x 256 tiles would leave most of the chip
 // idle on (fp8lin_gemm_stream.hip), with tiles of 16 mb x 16 nb outputs (K a
-// multiple of 128, 16-byte aligned operands).  stream_tile: its best tile and
-// the estimated time in us.  stream_tile_at: the tiles the kernel is built
-// for, i = 0, 1, ...; false past the last one.
-double stream_tile(int64_t M, int64_t N, int64_t K, int* mb, int* nb);
+// multiple of 128, 16-byte aligned operands).  stream_tile: its best tile,
+// and the estimated time in us without the amax.  stream_tile_at: the tiles
+// the kernel is built for, i = 0, 1, ...; false past the last one.
+double stream_tile(int64_t M, int64_t N, int64_t K, bool with_amax, int* mb, int* nb);
+int64_t stream_workgroups(int64_t M, int64_t N, int mb, int nb);
 bool stream_tile_at(int i, int* mb, int* nb);
 void launch_gemm_stream(int fa, int fb, int mb, int nb, const MmArgs& a, hipStream_t s);
 
 // Which kernel a matmul takes, and its tile in 16-row blocks if it is the
-// small-tile kernel: a function of the sizes alone.
+// small-tile kernel.  The kernel and the order of its sums depend on the sizes
+// alone, the tile also on whether the epilogue takes the output's amax.
 enum MmKernel { kMmRagged = 0, kMmStream = 1, kMm256 = 2 };
 struct MmRoute {
     int kernel, mb, nb;
 };
-MmRoute mm_route(int64_t M, int64_t N, int64_t K);
+MmRoute mm_route(int64_t M, int64_t N, int64_t K, bool with_amax);
 
 // C[m, n] = 2^-(*ba + *bb) * sum_k A[m, k] * B[n, k]; A [M, K] (format fa),
 // B [N, K] (format fb), both dense and, if K > 0, starting on 16-byte
@@ -146,9 +149,10 @@ int32_t launch_bias_mode(const int32_t* bias, int64_t n, int32_t* ring, int64_t 
                          hipStream_t s);
 
 // launch_gemm_nt with the epilogue amax of C turned into the Eq. 3 bias for
-// format bfmt in the same launch: the last workgroup to finish computes it
-// from a running maximum in ws[0..1], which must be zero and is left zero.
-// amax_bits and flags may be null.
+// format bfmt in the same launch (the last workgroup to finish computes it)
+// or, for many small tiles, in a launch of one thread after it, from a running
+// maximum in ws[0..1], which must be zero and is left zero.  amax_bits and
+// flags may be null.
 int32_t launch_gemm_nt_bias(const uint8_t* A, int fa, const int32_t* ba, const uint8_t* B, int fb,
                             const int32_t* bb, void* C, int out_dt, int64_t M, int64_t N, int64_t K, int bfmt,
                             int32_t margin, int32_t* bias, uint32_t* amax_bits, uint32_t* flags, uint32_t* ws,

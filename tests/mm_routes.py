@@ -17,22 +17,33 @@ def _lib():
         from paper_2309_17224_amd import build
         build.build()
     L = F.lib()
-    L.fp8lin_mm_route.argtypes = [_i64, _i64, _i64, _vp, _vp]
+    L.fp8lin_mm_route.argtypes = [_i64, _i64, _i64, _i32, _vp, _vp]
     L.fp8lin_mm_tile.argtypes = [_i32, _vp, _vp]
     L.fp8lin_mm_forced.argtypes = [_i32, _i32, _i32, _vp, _i32, _vp, _vp, _i32, _vp, _vp, _i32, _i64, _i64, _i64, _i32,
                                    _i32, _vp, _vp, _vp, _vp, ctypes.c_size_t, _vp]
     return L
 
 
-def route(M: int, N: int, K: int):
-    """(kernel, mb, nb): tiles of 16 mb x 16 nb outputs for STREAM, else zeros."""
+def route(M: int, N: int, K: int, with_amax: bool = False):
+    """(kernel, mb, nb): tiles of 16 mb x 16 nb outputs for STREAM, else zeros.
+    with_amax: of a call that takes the amax or the bias of its output."""
     mb, nb = _i32(), _i32()
-    kernel = _lib().fp8lin_mm_route(M, N, K, ctypes.byref(mb), ctypes.byref(nb))
+    kernel = _lib().fp8lin_mm_route(M, N, K, int(with_amax), ctypes.byref(mb), ctypes.byref(nb))
     return kernel, mb.value, nb.value
 
 
 def kernel(M: int, N: int, K: int) -> int:
     return route(M, N, K)[0]
+
+
+def stage(mb: int, nb: int) -> int:
+    """Bytes of k per stage of a small tile: tiles of one stage length sum in
+    one order, and 128 in that of the 256 x 256 kernel."""
+    return 512 if mb + nb <= 6 else 256 if mb + nb <= 12 else 128
+
+
+def workgroups(M: int, N: int, mb: int, nb: int) -> int:
+    return -(-M // (16 * mb)) * -(-N // (16 * nb))
 
 
 def tiles():

@@ -1,6 +1,7 @@
 """fp8_linear_fwd_bias / fp8_linear_bwd_dx_bias: the matmul with the Eq. 3
 bias of its output taken in the same launch (the last workgroup folds the
-running maximum into amax, bias and flags).
+running maximum into amax, bias and flags) or, for many small tiles, in a
+launch of one thread after it.
 
 Bar: bit-exact against the unfused calls (the matmul with its epilogue amax,
 then fp8_bias_from_amax), for every format and margin, bf16 and fp32 outputs,
@@ -90,6 +91,24 @@ def test_dx_bias_matches_unfused(gpu, shape, fmt):
         assert torch.equal(dx.view(torch.int16), dx0.view(torch.int16))
         assert (i32(b), u32(a), u32(fl)) == (i32(b0), u32(amax), u32(f0))
         assert not ws.any()
+
+
+# The plain product and the one with a bias take different tiles; the bias comes
+# from the launch itself (few workgroups) or from one after it (more than 64).
+@pytest.mark.parametrize("shape", [(33, 768, 768), (256, 768, 768), (100, 2304, 768), (1024, 768, 768), (301, 4096, 4096),
+                                   (130, 200, 100), (700, 1000, 100)], ids=str)
+def test_output_bits_do_not_depend_on_the_bias(gpu, shape):
+    M, N, K = shape
+    x8, bx, w8t, bw = operands(gpu, M, N, K, 3 * M + N)
+    y0 = F.fp8_linear_fwd(x8, bx, w8t, bw, out_dt=F.DT_F32)
+    y1, b1, a1, f1 = unfused_fwd(x8, bx, w8t, bw, F.E4M3, 1, F.DT_F32)
+    ws = F.bias_workspace(gpu)
+    for _ in range(2):  # the workspace is left as it was
+        y2, b2, a2, f2 = F.fp8_linear_fwd_bias(x8, bx, w8t, bw, F.E4M3, 1, out_dt=F.DT_F32, ws=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(bits(y0), bits(y1)) and torch.equal(bits(y0), bits(y2))
+        assert (i32(b1), u32(a1), u32(f1)) == (i32(b2), u32(a2), u32(f2)) and not ws.any()
+        assert u32(a2) == int(y0.abs().max().view(torch.int32))
 
 
 def test_workspace_reuse_across_calls_and_shapes(gpu):

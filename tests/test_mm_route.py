@@ -26,3 +26,19 @@ def test_products_faster_in_small_tiles_take_them(shape):
 def test_rows_of_a_decode_and_odd_contractions():
     assert all(R.kernel(m, n, 4096) == R.STREAM for m in (1, 16, 32) for n in (64, 4096, 57344))
     assert all(R.kernel(512, 4096, k) == R.RAGGED for k in (1, 127, 4032, 4097, 1 << 22))
+
+
+def test_amax_changes_the_tile_but_not_the_order_of_the_sums():
+    """Each workgroup's fold of its maximum waits for the others', so calls that
+    take the amax use fewer, larger tiles, of the same stage length."""
+    for m in (1, 16, 33, 64, 100, 160, 256, 400, 717, 1024, 1531, 2048):
+        for n in (512, 768, 1024, 2304, 4096, 12288):
+            for k in (128, 512, 768, 1024, 3072, 4096):
+                (kp, *tp), (ka, *ta) = R.route(m, n, k), R.route(m, n, k, with_amax=True)
+                assert kp == ka, (m, n, k)
+                if kp == R.STREAM:
+                    assert R.stage(*tp) == R.stage(*ta), (m, n, k)
+                    assert R.workgroups(m, n, *ta) <= R.workgroups(m, n, *tp), (m, n, k)
+    # with the tile that is best without an amax: 22, 17.8 and 25 us with an in-launch bias
+    for (m, n, k), most in {(256, 768, 768): 150, (64, 3072, 768): 200, (33, 4096, 4096): 256}.items():
+        assert R.workgroups(m, n, *R.route(m, n, k, with_amax=True)[1:]) <= most
