@@ -749,8 +749,45 @@ __global__ __launch_bounds__(64 * kRowWaves) void row_max_kernel(const void* __r
     if (lane == 0) rmax[r] = m;
 }
 
-// Few segments take wide workgroups (long segments), many take narrow ones
-// (more of them resident).
+// One segment [b0, b1) as thread tid of nth, which all call it: the maximum of
+// its rows' words, Eq. 3, and the bias over the words.  reduce: the maximum
+// over the nth threads.
+template <int DT, int FMT, int NTH, typename Reduce>
+__device__ __forceinline__ void seg_finish(int64_t seg, int64_t b0, int64_t b1, int tid, int32_t margin,
+                                           int32_t* __restrict__ bias, uint32_t* __restrict__ amax,
+                                           uint32_t* __restrict__ flags, uint32_t* __restrict__ rowb, Reduce reduce) {
+    uint32_t m = 0;
+    for (int64_t i = b0 + tid; i < b1; i += 4 * NTH) {
+        uint32_t v[4];
+#pragma unroll
+        for (int l = 0; l < 4; ++l) v[l] = rowb[min(i + l * NTH, b1 - 1)];
+        m = max(m, max(max(v[0], v[1]), max(v[2], v[3])));
+    }
+    m = reduce(m);
+    const uint32_t a32 = canon_amax(DT == FP8_DT_BF16 ? m << 16 : m);
+    uint32_t fl;
+    const int32_t b = bias_of<FMT>(a32, margin, &fl);
+    if (tid == 0) {
+        bias[seg] = b;
+        amax[seg] = a32;
+        if (flags) flags[seg] = fl;
+    }
+    for (int64_t i = b0 + tid; i < b1; i += NTH) rowb[i] = (uint32_t)b;
+}
+
+// Maximum over a workgroup of NTH threads; red may be reused after the next barrier.
+template <int NTH>
+__device__ __forceinline__ uint32_t wg_max(uint32_t m, uint32_t* red) {
+    m = wave_max(m);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NTH / 64; ++w) m = max(m, red[w]);
+    return m;
+}
+
+// A workgroup per segment.  Few segments take wide workgroups (long
+// segments), more take narrow ones (more of them resident).
 template <int DT, int FMT, int kSegThreads>
 __global__ __launch_bounds__(kSegThreads) void seg_bias_kernel(const int32_t* __restrict__ off, int64_t rows,
                                                                int32_t margin, int32_t* __restrict__ bias,
@@ -759,27 +796,45 @@ __global__ __launch_bounds__(kSegThreads) void seg_bias_kernel(const int32_t* __
     __shared__ uint32_t red[kSegThreads / 64];
     const int64_t b0 = min(max((int64_t)off[blockIdx.x], (int64_t)0), rows);
     const int64_t b1 = min(max((int64_t)off[blockIdx.x + 1], b0), rows);
-    uint32_t m = 0;
-    for (int64_t i = b0 + threadIdx.x; i < b1; i += 4 * kSegThreads) {
-        uint32_t v[4];
-#pragma unroll
-        for (int l = 0; l < 4; ++l) v[l] = rowb[min(i + l * kSegThreads, b1 - 1)];
-        m = max(m, max(max(v[0], v[1]), max(v[2], v[3])));
+    seg_finish<DT, FMT, kSegThreads>(blockIdx.x, b0, b1, threadIdx.x, margin, bias, amax, flags, rowb,
+                                     [&](uint32_t m) { return wg_max<kSegThreads>(m, red); });
+}
+
+// Very many segments (short ones on average): a wave per segment, four at a
+// time per workgroup, over a bounded grid; a segment of more than
+// kSegWaveRows rows is taken by the whole workgroup.  A workgroup per segment
+// spends its time on launching workgroups, and from 2^24 segments on is more
+// than one launch holds.
+// Up to kSegMany a workgroup per segment is as fast (20000 rows in 4000
+// segments: 18.1 us) and takes a long one among short ones with all its waves;
+// beyond, 20000 x 64 in 20000: 27.7 -> 20.7 us, 10^6 x 64 in 10^6: 928 -> 528.
+constexpr int kSegWaves = 4, kSegWaveRows = 1024, kSegManyBlocks = 16384, kSegMany = 4096;
+
+template <int DT, int FMT>
+__global__ __launch_bounds__(64 * kSegWaves) void seg_bias_many_kernel(const int32_t* __restrict__ off, int64_t nseg,
+                                                                       int64_t rows, int32_t margin,
+                                                                       int32_t* __restrict__ bias,
+                                                                       uint32_t* __restrict__ amax,
+                                                                       uint32_t* __restrict__ flags,
+                                                                       uint32_t* __restrict__ rowb) {
+    __shared__ uint32_t red[kSegWaves];
+    __shared__ int64_t bound[kSegWaves + 1];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (int64_t s0 = (int64_t)blockIdx.x * kSegWaves; s0 < nseg; s0 += (int64_t)gridDim.x * kSegWaves) {
+        __syncthreads();  // bound and red are free
+        if (threadIdx.x <= kSegWaves)
+            bound[threadIdx.x] = min(max((int64_t)off[min(s0 + threadIdx.x, nseg)], (int64_t)0), rows);
+        __syncthreads();
+        if (s0 + w < nseg && bound[w + 1] - bound[w] <= kSegWaveRows)
+            seg_finish<DT, FMT, 64>(s0 + w, bound[w], max(bound[w], bound[w + 1]), lane, margin, bias, amax, flags, rowb,
+                                    [](uint32_t m) { return wave_max(m); });
+        for (int j = 0; j < kSegWaves && s0 + j < nseg; ++j) {  // the same for every thread
+            if (bound[j + 1] - bound[j] <= kSegWaveRows) continue;
+            seg_finish<DT, FMT, 64 * kSegWaves>(s0 + j, bound[j], bound[j + 1], threadIdx.x, margin, bias, amax, flags,
+                                                rowb, [&](uint32_t m) { return wg_max<64 * kSegWaves>(m, red); });
+            __syncthreads();  // red is read
+        }
     }
-    m = wave_max(m);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < kSegThreads / 64; ++w) m = max(m, red[w]);
-    const uint32_t a32 = canon_amax(DT == FP8_DT_BF16 ? m << 16 : m);
-    uint32_t fl;
-    const int32_t b = bias_of<FMT>(a32, margin, &fl);
-    if (threadIdx.x == 0) {
-        bias[blockIdx.x] = b;
-        amax[blockIdx.x] = a32;
-        if (flags) flags[blockIdx.x] = fl;
-    }
-    for (int64_t i = b0 + threadIdx.x; i < b1; i += kSegThreads) rowb[i] = (uint32_t)b;
 }
 
 template <int DT, int FMT>
@@ -805,6 +860,10 @@ void launch_quantise_segments_t(const void* x, int64_t rows, int64_t cols, int64
     if (nseg <= 64)
         hipLaunchKernelGGL((seg_bias_kernel<DT, FMT, 1024>), dim3((unsigned)nseg), dim3(1024), 0, s, off, rows, margin, bias,
                            amax, flags, rmax);
+    else if (nseg > kSegMany)
+        hipLaunchKernelGGL((seg_bias_many_kernel<DT, FMT>),
+                           dim3((unsigned)std::min<int64_t>(((int64_t)nseg + kSegWaves - 1) / kSegWaves, kSegManyBlocks)),
+                           dim3(64 * kSegWaves), 0, s, off, (int64_t)nseg, rows, margin, bias, amax, flags, rmax);
     else
         hipLaunchKernelGGL((seg_bias_kernel<DT, FMT, 256>), dim3((unsigned)nseg), dim3(256), 0, s, off, rows, margin, bias,
                            amax, flags, rmax);

@@ -54,6 +54,42 @@ def test_segments_match_oracle(orc, gpu, shape, layout, fmt):
         assert np.array_equal(q.cpu().numpy(), oq) and np.array_equal(qT.cpu().numpy(), oqT)
 
 
+@pytest.mark.parametrize("nseg", [4096, 4097, 9001])
+def test_many_segments_long_and_short(orc, gpu, nseg):
+    """A segment per wave (over 4096 of them), one longer than a wave takes,
+    empty ones, and a last group of fewer than four."""
+    rng = np.random.default_rng(nseg)
+    sizes = rng.integers(0, 3, size=nseg)
+    sizes[[0, 7, nseg - 1]] = 1100, 1024, 1025
+    off = np.concatenate([[0], np.cumsum(sizes)]).tolist()
+    x = data(off[-1], 24, nseg, F.DT_BF16)
+    q, qT, b, a, fl, rb = F.fp8_quantise_segments(x.to(gpu), torch.tensor(off, dtype=torch.int32, device=gpu), F.E4M3, 1,
+                                                  want_qT=True)
+    torch.cuda.synchronize()
+    oq, oqT, ob, oa, ofl, orb = orc.quantise_segments(host(x), off, F.E4M3, 1)
+    assert b.cpu().tolist() == ob and (a.cpu().numpy().view(np.uint32) == np.array(oa, dtype=np.uint32)).all()
+    assert (fl.cpu().numpy().view(np.uint32) == np.array(ofl, dtype=np.uint32)).all()
+    assert np.array_equal(rb.cpu().numpy(), orb)
+    assert np.array_equal(q.cpu().numpy(), oq) and np.array_equal(qT.cpu().numpy(), oqT)
+
+
+def test_more_segments_than_a_launch_has_workgroups(gpu):
+    nseg, rows = (1 << 24) + 3, 2000
+    x = data(rows, 16, 3, F.DT_BF16).to(gpu)
+    off = torch.zeros(nseg + 1, dtype=torch.int32, device=gpu)
+    off[6:], off[(1 << 24) + 1:], off[-1] = 3, 1500, rows  # segments 5, 2^24 and the last one
+    q, _, b, a, fl, rb = F.fp8_quantise_segments(x, off, F.E4M3)
+    torch.cuda.synchronize()
+    full = torch.ones(nseg, dtype=torch.bool, device=gpu)
+    for s, r0, r1 in ((5, 0, 3), (1 << 24, 3, 1500), (nseg - 1, 1500, rows)):
+        q0, _, b0, a0, f0 = F.fp8_quantise(x[r0:r1], F.E4M3)
+        torch.cuda.synchronize()
+        assert (i32(b[s]), u32(a[s]), u32(fl[s])) == (i32(b0), u32(a0), u32(f0))
+        assert torch.equal(q[r0:r1], q0) and bool((rb[r0:r1] == b0).all())
+        full[s] = False
+    assert not b[full].any() and not a[full].any() and bool((fl[full] == F.FLAG_ZERO).all())
+
+
 def test_one_segment_equals_whole_tensor_quantise(gpu):
     x = data(2048, 1536, 5, F.DT_BF16).to(gpu)
     offsets = torch.tensor([0, 2048], dtype=torch.int32, device=gpu)
