@@ -153,7 +153,8 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
     // real elements cannot change the maximum), so only the columns of a
     // lane's block decide how it loads: eight whole columns, the last ones of
     // the row (one vector ending at the row's end, moved down, zeros beyond),
-    // or, in rows of fewer than eight columns, element by element.  One lane
+    // or, in a single row and in rows of fewer than eight columns, element by
+    // element.  One lane
     // on a partial block used to go element by element, 64 guarded loads in a
     // row, and kept the whole launch waiting; transposed codes with an odd row
     // stride left as single bytes.  fp8_quantise of 301 x 4096: 13.0 -> 7.2 us;
@@ -164,7 +165,30 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
     const bool whole = !EDGE || (R0 + kCastRows <= rows && C0 + kCastCols <= cols);  // of the tile: uniform
     int64_t at = (whole ? r0 : min(r0, last)) * ldx + c0;
     auto next_row = [&](int i) { at += whole || r0 + i < last ? ldx : 0; };
-    if (!EDGE || cols >= 8) {
+    // codes of eight elements of row i
+    auto put_bf16 = [&](int i, const uint4& v) {
+        lo[i] = cast4_bf16<FMT>(v.x, v.y, bi[i]);
+        hi[i] = cast4_bf16<FMT>(v.z, v.w, bi[i]);
+        if (__builtin_expect(any_nan_bf16(v.x, v.y) || any_nan_bf16(v.z, v.w), 0)) {
+            const uint32_t h0[4] = {v.x & 0xFFFFu, v.x >> 16, v.y & 0xFFFFu, v.y >> 16};
+            const uint32_t h1[4] = {v.z & 0xFFFFu, v.z >> 16, v.w & 0xFFFFu, v.w >> 16};
+            lo[i] = nan_patch<FMT>(lo[i], h0);
+            hi[i] = nan_patch<FMT>(hi[i], h1);
+        }
+    };
+    auto put_f32 = [&](int i, const uint4& a, const uint4& bb) {
+        if (MAX) mag = fold_f32(fold_f32(mag, a), bb);
+        lo[i] = cast4_f32<FMT>(a, bi[i]);
+        hi[i] = cast4_f32<FMT>(bb, bi[i]);
+        const uint32_t m = (a.x | a.y | a.z | a.w | bb.x | bb.y | bb.z | bb.w) & 0x7F800000u;
+        if (__builtin_expect(m == 0x7F800000u, 0)) {  // some exponent field may be all ones
+            const uint32_t h0[4] = {f32_key(a.x), f32_key(a.y), f32_key(a.z), f32_key(a.w)};
+            const uint32_t h1[4] = {f32_key(bb.x), f32_key(bb.y), f32_key(bb.z), f32_key(bb.w)};
+            lo[i] = nan_patch<FMT>(lo[i], h0);
+            hi[i] = nan_patch<FMT>(hi[i], h1);
+        }
+    };
+    if (!EDGE || (cols >= 8 && rows > 1)) {
         const int drop = whole || left >= 8 ? 0 : left > 0 ? (int)(8 - left) : 8;  // elements moved out
         at -= drop;
         if (DT == FP8_DT_BF16) {
@@ -190,16 +214,7 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
                 mag = max((uint32_t)mm.x, (uint32_t)mm.y);
             }
 #pragma unroll
-            for (int i = 0; i < kRpt; ++i) {
-                lo[i] = cast4_bf16<FMT>(v[i].x, v[i].y, bi[i]);
-                hi[i] = cast4_bf16<FMT>(v[i].z, v[i].w, bi[i]);
-                if (__builtin_expect(any_nan_bf16(v[i].x, v[i].y) || any_nan_bf16(v[i].z, v[i].w), 0)) {
-                    const uint32_t h0[4] = {v[i].x & 0xFFFFu, v[i].x >> 16, v[i].y & 0xFFFFu, v[i].y >> 16};
-                    const uint32_t h1[4] = {v[i].z & 0xFFFFu, v[i].z >> 16, v[i].w & 0xFFFFu, v[i].w >> 16};
-                    lo[i] = nan_patch<FMT>(lo[i], h0);
-                    hi[i] = nan_patch<FMT>(hi[i], h1);
-                }
-            }
+            for (int i = 0; i < kRpt; ++i) put_bf16(i, v[i]);
         } else {
             // All rows' loads in flight at once pay in the plain cast and in
             // small tensors, but cost the quantise of whole tiles, which also
@@ -227,16 +242,34 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
                     if (drop & 2) a = make_uint4(a.z, a.w, bb.x, bb.y), bb = make_uint4(bb.z, bb.w, 0u, 0u);
                     if (drop & 1) a = make_uint4(a.y, a.z, a.w, bb.x), bb = make_uint4(bb.y, bb.z, bb.w, 0u);
                 }
-                if (MAX) mag = fold_f32(fold_f32(mag, a), bb);
-                lo[i] = cast4_f32<FMT>(a, bi[i]);
-                hi[i] = cast4_f32<FMT>(bb, bi[i]);
-                const uint32_t m = (a.x | a.y | a.z | a.w | bb.x | bb.y | bb.z | bb.w) & 0x7F800000u;
-                if (__builtin_expect(m == 0x7F800000u, 0)) {  // some exponent field may be all ones
-                    const uint32_t h0[4] = {f32_key(a.x), f32_key(a.y), f32_key(a.z), f32_key(a.w)};
-                    const uint32_t h1[4] = {f32_key(bb.x), f32_key(bb.y), f32_key(bb.z), f32_key(bb.w)};
-                    lo[i] = nan_patch<FMT>(lo[i], h0);
-                    hi[i] = nan_patch<FMT>(hi[i], h1);
+                put_f32(i, a, bb);
+            }
+        }
+    } else if (rows == 1) {
+        // A single row (a vector, a token): its 16 lanes read it once, where
+        // every lane of a partial tile reads eight rows (cast of 1 x 80000 fp32:
+        // 8.9 -> 2.8 us, 1 x 4096 bf16: 4.0 -> 2.5).  Columns past the last one read it again and become
+        // zero, so that the loads need no branch of a lane.
+#pragma unroll
+        for (int i = 0; i < kRpt; ++i) lo[i] = hi[i] = 0;
+        if (lr == 0 && left > 0) {
+            uint32_t e[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int64_t c = min(c0 + j, cols - 1);
+                e[j] = DT == FP8_DT_BF16 ? ((const uint16_t*)x)[c] : ((const uint32_t*)x)[c];
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) e[j] = j < left ? e[j] : 0u;
+            if (DT == FP8_DT_BF16) {
+                const uint4 v = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+                if (MAX) {
+                    const us2 mm = fold_bf16(us2{0, 0}, v);
+                    mag = max((uint32_t)mm.x, (uint32_t)mm.y);
                 }
+                put_bf16(0, v);
+            } else {
+                put_f32(0, make_uint4(e[0], e[1], e[2], e[3]), make_uint4(e[4], e[5], e[6], e[7]));
             }
         }
     } else {
@@ -569,8 +602,8 @@ void launch_cast_t(const void* x, int64_t rows, int64_t cols, int64_t ldx, const
 
 constexpr int kQuantPass2MaxBlocks = 1024;
 
-// Largest tensor (bytes) quantised in one launch: 1 x 4096 bf16 takes 4.1 us
-// against 7.5 with two launches, 16 x 4096 (128 KiB) 5.6 against 7.1, 16 x 8192
+// Largest tensor (bytes) quantised in one launch: 1 x 4096 bf16 takes 3.3 us
+// against 5.8 with two launches, 16 x 4096 (128 KiB) 5.6 against 7.1, 16 x 8192
 // (256 KiB) 8.3 against 7.1 (a workgroup pulls about 60 GB/s from L2).
 constexpr int64_t kSmallBytes = 160 << 10;
 

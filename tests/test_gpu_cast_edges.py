@@ -19,7 +19,7 @@ from parity_util import i32, np_bits, u32
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(1, 1), (1, 9), (3, 7), (5, 128), (127, 129), (128, 120), (129, 127), (136, 8), (45, 300), (301, 264), (255, 1001),
+SHAPES = [(1, 1), (1, 5), (1, 9), (1, 129), (1, 40001), (3, 7), (5, 128), (127, 129), (128, 120), (129, 127), (136, 8), (45, 300), (301, 264), (255, 1001),
           (20, 4096), (21, 4096), (4099, 8), (9103, 9), (1025, 129), (1001, 1000), (384, 256)]
 
 
@@ -68,6 +68,29 @@ def test_tile_edges(orc, gpu, shape, strided, dtype, fmt):
         assert (i32(b), u32(a), u32(fl)) == (ob, oa, ofl), f"prediction {pred}"
         assert np.array_equal(q.cpu().numpy(), oq) and np.array_equal(qT.cpu().numpy(), oqT), f"prediction {pred}"
         assert guard_kept(bq, rows, cols, pad) and guard_kept(bt, cols, rows, pad)
+
+
+@pytest.mark.parametrize("cols", [3, 8, 13, 260])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
+@pytest.mark.parametrize("fmt", [F.E4M3, F.E5M2, F.E4_A, F.E5_A])
+def test_special_values_in_one_row(orc, gpu, cols, dtype, fmt):
+    """A single row has loads of its own: zeros, infinities and NaN of both
+    signs in its first and last columns, by quantise and by cast."""
+    x = wl.small(1, cols, 1.0, cols).to(dtype)
+    for bad in ([], [float("inf")], [float("nan"), -0.0, float("-inf")]):
+        for j, v in enumerate(bad):
+            x[0, (0, cols - 1, cols // 2)[j]] = v
+        if len(bad) == 3:
+            x[0, cols - 1] = -torch.tensor(float("nan"))
+        xb = np_bits(x)
+        ob, oa, ofl = orc.scale_bias(xb, fmt, 1)
+        oq, oqT = orc.cast(xb, fmt, ob, transpose=True)
+        q, qT, b, a, fl = F.fp8_quantise(x.to(gpu), fmt, 1, want_qT=True)
+        q2, qT2 = F.fp8_cast(x.to(gpu), fmt, b, want_qT=True)
+        torch.cuda.synchronize()
+        assert (i32(b), u32(a), u32(fl)) == (ob, oa, ofl)
+        for got, ref in ((q, oq), (q2, oq), (qT, oqT), (qT2, oqT)):
+            assert np.array_equal(got.cpu().numpy(), ref)
 
 
 @pytest.mark.parametrize("n", [1, 7, 2049, 100003])
