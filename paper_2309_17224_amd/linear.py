@@ -44,6 +44,16 @@ class LinearBuffers:
     ws: torch.Tensor
     bws: torch.Tensor | None = None  # zeros between calls: in-launch biases of y and dx
 
+    def __post_init__(self):
+        # What a caller's own buffers lack is allocated here, once: a ws of
+        # workspace(n) has a word per block of fp8_scale_bias, the quantise
+        # needs one per 128 x 128 tile.
+        need = max(F.fp8_quantise_ws_bytes(r, c) for r, c in ((self.M, self.K), (self.K, self.N), (self.M, self.N)))
+        enough = self.ws.numel() * self.ws.element_size() >= need
+        self.qws = self.ws if enough else torch.empty(need, dtype=torch.uint8, device=self.device)
+        if self.bws is None:
+            self.bws = F.bias_workspace(self.device)
+
     # views into scal
     @property
     def bw(self): return self.scal[0:1]
@@ -110,18 +120,18 @@ def _quantise(x: torch.Tensor, fmt: int, margin: int, bias, amax, flags, q, qT, 
 def quantise_weight(w: torch.Tensor, b: LinearBuffers) -> None:
     """bias + cast of the weight: after every weight update (Sec. 3.2), or
     once at checkpoint load (Sec. 3.1)."""
-    _quantise(w, F.E4M3, 0, b.bw, b.amax_w, b.flags_w, b.w8, b.w8t, b.ws)
+    _quantise(w, F.E4M3, 0, b.bw, b.amax_w, b.flags_w, b.w8, b.w8t, b.qws)
 
 
 def forward(x: torch.Tensor, b: LinearBuffers, keep_xt: bool = True) -> torch.Tensor:
-    _quantise(x, F.E4M3, 0, b.bx, b.amax_x, b.flags_x, b.x8, b.x8t if keep_xt else None, b.ws)
+    _quantise(x, F.E4M3, 0, b.bx, b.amax_x, b.flags_x, b.x8, b.x8t if keep_xt else None, b.qws)
     F.fp8_linear_fwd_bias(b.x8, b.bx, b.w8t, b.bw, F.E4M3, 0, y=b.y, bias=b.by, amax_bits=b.amax_y, flags=b.flags_y,
                           ws=b.bws)
     return b.y
 
 
 def backward(dy: torch.Tensor, b: LinearBuffers, margin: int = 0):
-    _quantise(dy, F.E5M2, margin, b.bg, b.amax_g, b.flags_g, b.dy8, b.dy8t, b.ws)
+    _quantise(dy, F.E5M2, margin, b.bg, b.amax_g, b.flags_g, b.dy8, b.dy8t, b.qws)
     F.fp8_linear_bwd_dx_bias(b.dy8, b.bg, b.w8, b.bw, F.E5M2, margin, dx=b.dx, bias=b.bdx, amax_bits=b.amax_dx,
                              flags=b.flags_dx, ws=b.bws)
     F.fp8_linear_bwd_dw(b.x8t, b.bx, b.dy8t, b.bg, dw=b.dw)
@@ -140,7 +150,7 @@ def train_step(x: torch.Tensor, w: torch.Tensor, dy: torch.Tensor, b: LinearBuff
 def infer_step(x: torch.Tensor, b: LinearBuffers) -> torch.Tensor:
     """PTQ inference call: activation bias + cast, then the forward matmul
     with the weight quantised beforehand (quantise_weight / ptq)."""
-    _quantise(x, F.E4M3, 0, b.bx, b.amax_x, b.flags_x, b.x8, None, b.ws)
+    _quantise(x, F.E4M3, 0, b.bx, b.amax_x, b.flags_x, b.x8, None, b.qws)
     F.fp8_linear_fwd(b.x8, b.bx, b.w8t, b.bw, y=b.y)
     return b.y
 

@@ -63,3 +63,25 @@ def test_step_refuses_strided_tensors(gpu):
     b = L.alloc(16, 32, 64, gpu)
     with pytest.raises(ValueError):
         L.infer_step(wl.small(16, 64, 1.0, 1).to(gpu)[:, :32], b)
+
+
+def test_buffers_made_by_hand(gpu):
+    """Buffers without the in-launch bias workspace and with one that only
+    fp8_scale_bias's partials fill (4096 x 8 has fewer of them than tiles): the
+    same step, and nothing allocated by it."""
+    M, K, N = 4096, 8, 16
+    full = L.alloc(M, K, N, gpu)
+    assert F.fp8_scale_bias_ws_bytes(M * N) < F.fp8_quantise_ws_bytes(M, N)
+    names = ("w8", "w8t", "x8", "x8t", "dy8", "dy8t", "y", "dx", "dw", "scal")
+    own = L.LinearBuffers(M, K, N, gpu, *(torch.zeros_like(getattr(full, n)) for n in names), F.workspace(M * N, gpu))
+    x, w, dy = (wl.small(r, c, s, r + c).to(gpu) for r, c, s in ((M, K, 1.0), (K, N, 0.02), (M, N, 1e-3)))
+    L.train_step(x, w, dy, full)
+    L.train_step(x, w, dy, own)
+    torch.cuda.synchronize()
+    made = torch.cuda.memory_stats()["allocation.all.allocated"]
+    L.train_step(x, w, dy, own)
+    L.infer_step(x, own)
+    torch.cuda.synchronize()
+    assert torch.cuda.memory_stats()["allocation.all.allocated"] == made
+    for n in names:
+        assert torch.equal(bits(getattr(own, n)), bits(getattr(full, n))), n
