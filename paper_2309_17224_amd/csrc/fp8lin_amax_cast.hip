@@ -131,7 +131,9 @@ __device__ __forceinline__ uint32_t byte_of(uint32_t w, int j) { return (w >> (8
 // With ROWB, row r is cast with its own bias rowb[r] (clamped) instead of b.
 // EDGE = false: every tile of the tensor is whole (rows and columns multiples
 // of 128); the kernels that stream large tensors are built both ways, since
-// the edge code costs registers and with them 1-2 % of the bandwidth.
+// the edge code costs registers and with them 1-2 % of the bandwidth, in the
+// second pass of the quantise 10 % (4096 x 4096 fp32 without a prediction,
+// 133 registers against 126: 32.4 us and 29.8).
 template <int DT, int FMT, bool MAX, bool ROWB = false, bool EDGE = true>
 __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_t rows, int64_t cols,
                                               int64_t ldx, int b, uint8_t* __restrict__ q, int64_t ldq,
@@ -215,11 +217,18 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
             }
 #pragma unroll
             for (int i = 0; i < kRpt; ++i) put_bf16(i, v[i]);
+        } else if (MAX && !EDGE) {
+            // the compiler interleaves loads and conversions (see below)
+#pragma unroll
+            for (int i = 0; i < kRpt; ++i) {
+                const uint32_t* p = (const uint32_t*)x + (r0 + i) * ldx + c0;
+                const uint4 a = ld_stream(p), bb = ld_stream(p + 4);
+                put_f32(i, a, bb);
+            }
         } else {
             // All rows' loads in flight at once pay in the plain cast and in
             // small tensors, but cost the quantise of whole tiles, which also
-            // folds the maximum, its occupancy (5.05 -> 4.91 TB/s): there the
-            // compiler interleaves.
+            // folds the maximum, its occupancy (5.05 -> 4.91 TB/s).
             uint4 va[kRpt], vb[kRpt];
             const int64_t at0 = at;
             auto load = [&](int i) {
@@ -441,7 +450,7 @@ __global__ __launch_bounds__(kCastThreads) void quant_small_kernel(
 }
 
 // Pass 2 of one tensor as workgroup bid of nb: see quant_pass2_kernel.
-template <int DT, int FMT>
+template <int DT, int FMT, bool EDGE>
 __device__ __forceinline__ void quant_pass2_body(
     int bid, int nb, uint8_t* tile, uint32_t* red, uint32_t& amax_s, const void* __restrict__ x,
     int64_t rows, int64_t cols, int64_t ldx, const uint32_t* __restrict__ parts, int nparts,
@@ -463,10 +472,10 @@ __device__ __forceinline__ void quant_pass2_body(
     const int b = clamp_bias(bx);
     if (have_used && *used == b) return;  // pass 1 already wrote these codes
     for (int64_t t = bid; t < ncast; t += nb)
-        cast_tile<DT, FMT, false>(x, rows, cols, ldx, b, q, ldq, qT, ldqT, t / tiles_c, t % tiles_c, tile);
+        cast_tile<DT, FMT, false, false, EDGE>(x, rows, cols, ldx, b, q, ldq, qT, ldqT, t / tiles_c, t % tiles_c, tile);
 }
 
-template <int DT, int FMT>
+template <int DT, int FMT, bool EDGE>
 __global__ __launch_bounds__(kCastThreads) void quant_pass2_kernel(
     const void* __restrict__ x, int64_t rows, int64_t cols, int64_t ldx,
     const uint32_t* __restrict__ parts, int nparts, const int32_t* __restrict__ used, int have_used,
@@ -476,8 +485,8 @@ __global__ __launch_bounds__(kCastThreads) void quant_pass2_kernel(
     __shared__ __attribute__((aligned(16))) uint8_t tile[kCastCols * kCastRows];
     __shared__ uint32_t red[kCastThreads / 64];
     __shared__ uint32_t amax_s;
-    quant_pass2_body<DT, FMT>(blockIdx.x, gridDim.x, tile, red, amax_s, x, rows, cols, ldx, parts, nparts, used,
-                              have_used, margin, bias, amax_bits, flags, q, ldq, qT, ldqT, tiles_c, ncast);
+    quant_pass2_body<DT, FMT, EDGE>(blockIdx.x, gridDim.x, tile, red, amax_s, x, rows, cols, ldx, parts, nparts, used,
+                                    have_used, margin, bias, amax_bits, flags, q, ldq, qT, ldqT, tiles_c, ncast);
 }
 
 // ------------------------------------------------ delayed scaling
@@ -569,17 +578,17 @@ __global__ __launch_bounds__(kCastThreads) void quant_pass1_batch_kernel(QBatch 
     if (threadIdx.x == 0) qb.ws[i][1 + t] = bm;
 }
 
-template <int DT, int FMT>
+template <int DT, int FMT, bool EDGE>
 __global__ __launch_bounds__(kCastThreads) void quant_pass2_batch_kernel(QBatch qb, int32_t margin, int have_used) {
     __shared__ __attribute__((aligned(16))) uint8_t tile[kCastCols * kCastRows];
     __shared__ uint32_t red[kCastThreads / 64];
     __shared__ uint32_t amax_s;
     const int i = batch_slot(qb.p0, qb.n, blockIdx.x);
     const int64_t ntiles = qb.t0[i + 1] - qb.t0[i];
-    quant_pass2_body<DT, FMT>((int)(blockIdx.x - qb.p0[i]), (int)(qb.p0[i + 1] - qb.p0[i]), tile, red, amax_s,
-                              qb.x[i], qb.rows[i], qb.cols[i], qb.ldx[i], qb.ws[i] + 1, (int)ntiles,
-                              (const int32_t*)qb.ws[i], have_used, margin, qb.bias[i], qb.amax[i], qb.flags[i],
-                              qb.q[i], qb.ldq[i], qb.qT[i], qb.ldqT[i], qb.tiles_c[i], ntiles);
+    quant_pass2_body<DT, FMT, EDGE>((int)(blockIdx.x - qb.p0[i]), (int)(qb.p0[i + 1] - qb.p0[i]), tile, red, amax_s,
+                                    qb.x[i], qb.rows[i], qb.cols[i], qb.ldx[i], qb.ws[i] + 1, (int)ntiles,
+                                    (const int32_t*)qb.ws[i], have_used, margin, qb.bias[i], qb.amax[i], qb.flags[i],
+                                    qb.q[i], qb.ldq[i], qb.qT[i], qb.ldqT[i], qb.tiles_c[i], ntiles);
 }
 
 // fn(true_type) when some tile of a rows x cols tensor is partial.
@@ -618,7 +627,7 @@ void launch_quantise_t(const void* x, int64_t rows, int64_t cols, int64_t ldx, i
     int32_t* used = (int32_t*)ws;
     uint32_t* parts = ws + 1;
     constexpr int per = DT == FP8_DT_BF16 ? 8 : 4;
-    if (cols >= 8 && (ldx == cols || cols > per) && ntiles <= kQuantPass2MaxBlocks && rows * cols * (16 / per) <= kSmallBytes) {
+    if (cols >= 8 && (ldx == cols || cols > per) && rows * cols * (16 / per) <= kSmallBytes) {
         // dense: one row of all elements
         const int rows1 = ldx == cols ? 1 : (int)rows, cols1 = (int)(ldx == cols ? rows * cols : cols);
         const int vpr = (cols1 + per - 1) / per;
@@ -636,11 +645,11 @@ void launch_quantise_t(const void* x, int64_t rows, int64_t cols, int64_t ldx, i
         else
             hipLaunchKernelGGL((quant_pass1_kernel<DT, FMT, false, kE>), dim3((unsigned)ntiles), dim3(kCastThreads), 0, s,
                                x, rows, cols, ldx, bias_pred, used, parts, q, ldq, qT, ldqT, tiles_c);
+        const int nb2 = (int)(ntiles < kQuantPass2MaxBlocks ? ntiles : kQuantPass2MaxBlocks);
+        hipLaunchKernelGGL((quant_pass2_kernel<DT, FMT, kE>), dim3(nb2), dim3(kCastThreads), 0, s, x, rows, cols, ldx,
+                           parts, (int)ntiles, used, bias_pred ? 1 : 0, margin, bias, amax_bits, flags, q, ldq,
+                           qT, ldqT, tiles_c, ntiles);
     });
-    const int nb2 = (int)(ntiles < kQuantPass2MaxBlocks ? ntiles : kQuantPass2MaxBlocks);
-    hipLaunchKernelGGL((quant_pass2_kernel<DT, FMT>), dim3(nb2), dim3(kCastThreads), 0, s, x, rows, cols, ldx,
-                       parts, (int)ntiles, used, bias_pred ? 1 : 0, margin, bias, amax_bits, flags, q, ldq,
-                       qT, ldqT, tiles_c, ntiles);
 }
 
 template <int DT, int FMT>
@@ -678,9 +687,9 @@ void launch_quantise_batch_t(int n, const QuantDesc* d, int32_t margin, hipStrea
         else
             hipLaunchKernelGGL((quant_pass1_batch_kernel<DT, FMT, false, kE>), dim3((unsigned)qb.t0[n]),
                                dim3(kCastThreads), 0, s, qb);
+        hipLaunchKernelGGL((quant_pass2_batch_kernel<DT, FMT, kE>), dim3((unsigned)qb.p0[n]), dim3(kCastThreads), 0, s, qb,
+                           margin, pred ? 1 : 0);
     });
-    hipLaunchKernelGGL((quant_pass2_batch_kernel<DT, FMT>), dim3((unsigned)qb.p0[n]), dim3(kCastThreads), 0, s, qb,
-                       margin, pred ? 1 : 0);
 }
 
 template <int DT, int FMT>
@@ -691,8 +700,11 @@ void launch_quant_check_t(const void* x, int64_t rows, int64_t cols, int64_t ldx
     const int64_t tiles_c = (cols + kCastCols - 1) / kCastCols;
     const int64_t ncast = ((rows + kCastRows - 1) / kCastRows) * tiles_c;
     const int nb2 = (int)(ncast < kQuantPass2MaxBlocks ? ncast : kQuantPass2MaxBlocks);
-    hipLaunchKernelGGL((quant_pass2_kernel<DT, FMT>), dim3(nb2), dim3(kCastThreads), 0, s, x, rows, cols, ldx,
-                       parts, nparts, used, 1, margin, bias, amax_bits, flags, q, ldq, qT, ldqT, tiles_c, ncast);
+    with_edge(has_edge(rows, cols), [&](auto E) {
+        hipLaunchKernelGGL((quant_pass2_kernel<DT, FMT, decltype(E)::value>), dim3(nb2), dim3(kCastThreads), 0, s, x, rows,
+                           cols, ldx, parts, nparts, used, 1, margin, bias, amax_bits, flags, q, ldq, qT, ldqT, tiles_c,
+                           ncast);
+    });
 }
 
 template <int DT, int FMT>
