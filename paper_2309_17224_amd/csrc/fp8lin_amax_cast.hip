@@ -134,7 +134,9 @@ __device__ __forceinline__ uint32_t byte_of(uint32_t w, int j) { return (w >> (8
 // the edge code costs registers and with them 1-2 % of the bandwidth, in the
 // second pass of the quantise 10 % (4096 x 4096 fp32 without a prediction,
 // 133 registers against 126: 32.4 us and 29.8).
-template <int DT, int FMT, bool MAX, bool ROWB = false, bool EDGE = true>
+// BULK = false: fp32 rows of whole tiles load as the compiler interleaves them
+// with the conversions (see launch_cast_t).
+template <int DT, int FMT, bool MAX, bool ROWB = false, bool EDGE = true, bool BULK = true>
 __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_t rows, int64_t cols,
                                               int64_t ldx, int b, uint8_t* __restrict__ q, int64_t ldq,
                                               uint8_t* __restrict__ qT, int64_t ldqT, int64_t tr,
@@ -217,7 +219,7 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
             }
 #pragma unroll
             for (int i = 0; i < kRpt; ++i) put_bf16(i, v[i]);
-        } else if (MAX && !EDGE) {
+        } else if ((MAX || !BULK) && !EDGE) {
             // the compiler interleaves loads and conversions (see below)
 #pragma unroll
             for (int i = 0; i < kRpt; ++i) {
@@ -358,15 +360,15 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
 }
 
 
-template <int DT, int FMT, bool EDGE>
+template <int DT, int FMT, bool EDGE, bool BULK>
 __global__ __launch_bounds__(kCastThreads) void cast_kernel(
     const void* __restrict__ x, int64_t rows, int64_t cols, int64_t ldx,
     const int32_t* __restrict__ bias_p, uint8_t* __restrict__ q, int64_t ldq,
     uint8_t* __restrict__ qT, int64_t ldqT, int64_t tiles_c) {
     __shared__ __attribute__((aligned(16))) uint8_t tile[kCastCols * kCastRows];
     const int b = clamp_bias(*bias_p);
-    cast_tile<DT, FMT, false, false, EDGE>(x, rows, cols, ldx, b, q, ldq, qT, ldqT, blockIdx.x / tiles_c,
-                                           blockIdx.x % tiles_c, tile);
+    cast_tile<DT, FMT, false, false, EDGE, BULK>(x, rows, cols, ldx, b, q, ldq, qT, ldqT, blockIdx.x / tiles_c,
+                                                 blockIdx.x % tiles_c, tile);
 }
 
 // ------------------------------------------------- quantise: amax + bias + cast
@@ -598,14 +600,30 @@ void with_edge(bool edge, Fn&& fn) {
     if (edge) fn(std::true_type{}); else fn(std::false_type{});
 }
 
+// fp32 casts of whole tiles with all of a lane's loads in flight at once (90
+// registers), or interleaved with the conversions (about 60).  All at once
+// where few tiles leave the latency open (2048 x 4096: 9.3 us against 10.1) and
+// where the tensor comes from HBM and rows of codes leave (4096 x 11008 47.8
+// against 50.2, with both copies 58.1 against 60.9); interleaved from about two
+// tiles per compute unit to what the last-level cache holds (4096 x 8192 35.0
+// against 31.9, both copies 42.7 against 37.8; 2048 x 5120 12.4 against 11.8)
+// and for transposed codes alone (8192 x 8192 72.5 against 70.1).
+constexpr int64_t kBulkTiles = 512, kBulkTilesHbm = 2048;
+
 template <int DT, int FMT>
 void launch_cast_t(const void* x, int64_t rows, int64_t cols, int64_t ldx, const int32_t* bias,
                    uint8_t* q, int64_t ldq, uint8_t* qT, int64_t ldqT, hipStream_t s) {
     const int64_t tiles_r = (rows + kCastRows - 1) / kCastRows;
-    const int64_t tiles_c = (cols + kCastCols - 1) / kCastCols;
-    with_edge(has_edge(rows, cols), [&](auto E) {
-        hipLaunchKernelGGL((cast_kernel<DT, FMT, decltype(E)::value>), dim3((unsigned)(tiles_r * tiles_c)), dim3(kCastThreads),
-                           0, s, x, rows, cols, ldx, bias, q, ldq, qT, ldqT, tiles_c);
+    const int64_t tiles_c = (cols + kCastCols - 1) / kCastCols, ntiles = tiles_r * tiles_c;
+    const bool edge = has_edge(rows, cols);
+    if (DT == FP8_DT_F32 && !edge && ntiles > kBulkTiles && (ntiles <= kBulkTilesHbm || !q)) {
+        hipLaunchKernelGGL((cast_kernel<DT, FMT, false, DT != FP8_DT_F32>), dim3((unsigned)ntiles), dim3(kCastThreads), 0, s,
+                           x, rows, cols, ldx, bias, q, ldq, qT, ldqT, tiles_c);
+        return;
+    }
+    with_edge(edge, [&](auto E) {
+        hipLaunchKernelGGL((cast_kernel<DT, FMT, decltype(E)::value, true>), dim3((unsigned)ntiles), dim3(kCastThreads), 0, s,
+                           x, rows, cols, ldx, bias, q, ldq, qT, ldqT, tiles_c);
     });
 }
 

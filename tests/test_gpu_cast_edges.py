@@ -102,3 +102,26 @@ def test_scale_bias_unaligned(orc, gpu, n, dtype):
     b, a, fl = F.fp8_scale_bias(x.cuda()[1:], F.E4M3)
     torch.cuda.synchronize()
     assert (i32(b), u32(a), u32(fl)) == orc.scale_bias(np_bits(x[1:]), F.E4M3)
+
+
+@pytest.mark.parametrize("tiles", [512, 513, 2048, 2049])
+@pytest.mark.parametrize("want", ["q", "qT", "both"])
+def test_fp32_cast_of_many_whole_tiles(orc, gpu, tiles, want):
+    """Both ways of loading whole fp32 tiles, on both sides of where the choice
+    changes: the codes of 256 tiles at a time (which load one way), those of
+    the first ones the oracle's."""
+    rows, step = 128 * tiles, 128 * 256
+    x = torch.randn(rows, 128, generator=torch.Generator(gpu).manual_seed(tiles), device=gpu)
+    x[::97, 5] = float("nan")
+    x[3::101, 127] = -float("inf")
+    x[7::89, 64] *= 2.0 ** -20
+    b = torch.tensor([6], dtype=torch.int32, device=gpu)
+    for fmt in (F.E4M3, F.E5_A):
+        q, qT = F.fp8_cast(x, fmt, b, want_q=want != "qT", want_qT=want != "q")
+        for r in range(0, rows, step):
+            part, partT = F.fp8_cast(x[r:r + step], fmt, b, want_qT=True)
+            assert q is None or torch.equal(q[r:r + step], part)
+            assert qT is None or torch.equal(qT[:, r:r + step], partT)
+            if r == 0:
+                ref, refT = orc.cast(np_bits(x[:step].cpu()), fmt, 6, transpose=True)
+                assert np.array_equal(part.cpu().numpy(), ref) and np.array_equal(partT.cpu().numpy(), refT)
