@@ -93,7 +93,8 @@ def test_special_values_in_one_row(orc, gpu, cols, dtype, fmt):
             assert np.array_equal(got.cpu().numpy(), ref)
 
 
-@pytest.mark.parametrize("n", [1, 7, 2049, 100003])
+# (1024 elements are the most that are read one by one)
+@pytest.mark.parametrize("n", [1, 7, 1023, 1024, 1025, 2049, 100003])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
 def test_scale_bias_unaligned(orc, gpu, n, dtype):
     x = wl.small(1, n + 1, 1.0, n).to(dtype)[0]
@@ -125,3 +126,19 @@ def test_fp32_cast_of_many_whole_tiles(orc, gpu, tiles, want):
             if r == 0:
                 ref, refT = orc.cast(np_bits(x[:step].cpu()), fmt, 6, transpose=True)
                 assert np.array_equal(part.cpu().numpy(), ref) and np.array_equal(partT.cpu().numpy(), refT)
+
+
+@pytest.mark.parametrize("n", [1, 1024, 1025, 1031, 40000])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
+def test_scale_bias_finds_the_amax_anywhere(gpu, n, dtype):
+    """At every offset from a 16-byte boundary, the amax in the elements before
+    the first whole vector, after the last one, and inside."""
+    per = 8 if dtype == torch.bfloat16 else 4
+    for off in range(per + 1):
+        for at in sorted({0, min(per, n - 1), n // 2, n - 1, max(n - per, 0)}):
+            x = torch.zeros(n + per + 1, dtype=dtype, device=gpu)
+            x[:off] = float("nan")
+            x[off + n:] = float("nan")
+            x[off + at] = -3.0
+            _, a, _ = F.fp8_scale_bias(x[off:off + n], F.E4M3)
+            assert u32(a) == 0x40400000, (off, at)
