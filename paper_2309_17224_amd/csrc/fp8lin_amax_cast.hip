@@ -176,19 +176,31 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
     // real elements cannot change the maximum), so only the columns of a
     // lane's block decide how it loads: eight whole columns, the last ones of
     // the row (one vector ending at the row's end, moved down, zeros beyond),
-    // or, in a single row and in rows of fewer than eight columns, element by
-    // element.  One lane
-    // on a partial block used to go element by element, 64 guarded loads in a
+    // or those of a single row or of rows of fewer than eight columns (below);
+    // lanes with no row at all load nothing.  One lane on a partial block used to go element by element, 64 guarded loads in a
     // row, and kept the whole launch waiting; transposed codes with an odd row
     // stride left as single bytes.  fp8_quantise of 301 x 4096: 13.0 -> 7.2 us;
     // 1531 x 4096 with transposed codes: 25.0 -> 12.9 us; whole tiles as before
     // (4096 x 11008 with both copies 36 us, 5.0 TB/s).
     const int64_t last = rows - 1;
     const int64_t left = EDGE ? cols - c0 : 8;  // columns of the row from c0 on
+    const int nc = (int)min(cols, (int64_t)8);
     const bool whole = !EDGE || (R0 + kCastRows <= rows && C0 + kCastCols <= cols);  // of the tile: uniform
     int64_t at = (whole ? r0 : min(r0, last)) * ldx + c0;
     auto next_row = [&](int i) { at += whole || r0 + i < last ? ldx : 0; };
-    // codes of eight elements of row i
+    // codes of eight elements of row i, and of four
+    auto half_bf16 = [&](int i, uint32_t w0, uint32_t w1) {
+        const uint32_t c = cast4_bf16<FMT>(w0, w1, bi[i]);
+        if (__builtin_expect(!any_nan_bf16(w0, w1), 1)) return c;
+        const uint32_t h[4] = {w0 & 0xFFFFu, w0 >> 16, w1 & 0xFFFFu, w1 >> 16};
+        return nan_patch<FMT>(c, h);
+    };
+    auto half_f32 = [&](int i, const uint4& a) {
+        const uint32_t c = cast4_f32<FMT>(a, bi[i]);
+        if (__builtin_expect(((a.x | a.y | a.z | a.w) & 0x7F800000u) != 0x7F800000u, 1)) return c;
+        const uint32_t h[4] = {f32_key(a.x), f32_key(a.y), f32_key(a.z), f32_key(a.w)};  // some exponent may be all ones
+        return nan_patch<FMT>(c, h);
+    };
     auto put_bf16 = [&](int i, const uint4& v) {
         lo[i] = cast4_bf16<FMT>(v.x, v.y, bi[i]);
         hi[i] = cast4_bf16<FMT>(v.z, v.w, bi[i]);
@@ -211,7 +223,10 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
             hi[i] = nan_patch<FMT>(hi[i], h1);
         }
     };
-    if (!EDGE || (cols >= 8 && rows > 1)) {
+    if (EDGE && rows > 1 && r0 >= rows) {
+#pragma unroll
+        for (int i = 0; i < kRpt; ++i) lo[i] = hi[i] = 0;
+    } else if (!EDGE || (cols >= 8 && rows > 1)) {
         const int drop = whole || left >= 8 ? 0 : left > 0 ? (int)(8 - left) : 8;  // elements moved out
         at -= drop;
         if (DT == FP8_DT_BF16) {
@@ -302,21 +317,92 @@ __device__ __forceinline__ uint32_t cast_tile(const void* __restrict__ x, int64_
                 put_f32(0, make_uint4(e[0], e[1], e[2], e[3]), make_uint4(e[4], e[5], e[6], e[7]));
             }
         }
-    } else {
+    } else if (nc > 4) {
+        // Rows of five to seven columns: eight elements from the row's start on
+        // (in the last rows the tensor's last eight, moved down), those past
+        // the row's end zero.
 #pragma unroll
-        for (int i = 0; i < kRpt; ++i) {
-            uint32_t wlo = 0, whi = 0;
-            for (int j = 0; j < 8; ++j) {
-                uint32_t code = 0u;
-                if (j < left) {
-                    code = cast1<DT, FMT>(x, at + j, bi[i]);
-                    if (MAX) mag = max(mag, elem_mag<DT>(x, at + j));
+        for (int i = 0; i < kRpt; ++i) lo[i] = hi[i] = 0;
+        if (left > 0) {
+            const int64_t end8 = last * ldx + cols - 8;  // two rows or more: at least 2 cols - 8 > 0
+            us2 mm = {0, 0};
+#pragma unroll
+            for (int i0 = 0; i0 < kRpt; i0 += 4) {  // four rows in flight: no more registers than the other branches
+                uint4 va[4], vb[4];
+                int moved[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int64_t from = min(at, end8);
+                    moved[k] = (int)(at - from);
+                    if (DT == FP8_DT_BF16) {
+                        va[k] = ld_stream((const uint16_t*)x + from);
+                    } else {
+                        va[k] = ld_stream((const uint32_t*)x + from);
+                        vb[k] = ld_stream((const uint32_t*)x + from + 4);
+                    }
+                    next_row(i0 + k);
                 }
-                if (j < 4) wlo |= code << (8 * j); else whi |= code << (8 * (j - 4));
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (DT == FP8_DT_BF16) {
+                        auto keep = [&](int w) { return nc > 2 * w + 1 ? ~0u : nc > 2 * w ? 0xFFFFu : 0u; };
+                        uint4 v = moved[k] ? shr128(va[k], 16 * moved[k]) : va[k];
+                        v = make_uint4(v.x & keep(0), v.y & keep(1), v.z & keep(2), v.w & keep(3));
+                        if (MAX) mm = fold_bf16(mm, v);
+                        put_bf16(i0 + k, v);
+                    } else {
+                        uint4 a = va[k], bb = vb[k];
+                        if (moved[k] & 4) a = bb;  // what is left of bb lies past the row's end
+                        if (moved[k] & 2) a = make_uint4(a.z, a.w, bb.x, bb.y), bb = make_uint4(bb.z, bb.w, 0u, 0u);
+                        if (moved[k] & 1) a = make_uint4(a.y, a.z, a.w, bb.x), bb = make_uint4(bb.y, bb.z, bb.w, 0u);
+                        a = make_uint4(a.x, nc > 1 ? a.y : 0u, nc > 2 ? a.z : 0u, nc > 3 ? a.w : 0u);
+                        bb = make_uint4(nc > 4 ? bb.x : 0u, nc > 5 ? bb.y : 0u, nc > 6 ? bb.z : 0u, 0u);
+                        put_f32(i0 + k, a, bb);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
-            next_row(i);
-            lo[i] = wlo;
-            hi[i] = whi;
+            if (MAX && DT == FP8_DT_BF16) mag = max((uint32_t)mm.x, (uint32_t)mm.y);
+        }
+    } else {
+        // Rows of one to four columns: their elements, all loads in flight (cast
+        // of 10^6 x 4 bf16 one element after another 52 us, fp32 54; now 25 and
+        // 32; with the vectors of the branch above 38 and 48).
+#pragma unroll
+        for (int i = 0; i < kRpt; ++i) lo[i] = hi[i] = 0;
+        if (left > 0) {
+            uint32_t e[kRpt][4];
+            int64_t row[kRpt];
+#pragma unroll
+            for (int i = 0; i < kRpt; ++i) {
+                row[i] = at;
+                next_row(i);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+#pragma unroll
+                for (int i = 0; i < kRpt; ++i) e[i][j] = 0;
+                if (j < nc) {
+#pragma unroll
+                    for (int i = 0; i < kRpt; ++i)
+                        e[i][j] = DT == FP8_DT_BF16 ? ((const uint16_t*)x)[row[i] + j] : ((const uint32_t*)x)[row[i] + j];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < kRpt; ++i) {
+                if (DT == FP8_DT_BF16) {
+                    const uint32_t w0 = e[i][0] | (e[i][1] << 16), w1 = e[i][2] | (e[i][3] << 16);
+                    if (MAX) {
+                        const us2 mm = fold_bf16(us2{0, 0}, make_uint4(w0, w1, 0u, 0u));
+                        mag = max(mag, max((uint32_t)mm.x, (uint32_t)mm.y));
+                    }
+                    lo[i] = half_bf16(i, w0, w1);
+                } else {
+                    const uint4 a = make_uint4(e[i][0], e[i][1], e[i][2], e[i][3]);
+                    if (MAX) mag = fold_f32(mag, a);
+                    lo[i] = half_f32(i, a);
+                }
+            }
         }
     }
 
@@ -619,6 +705,16 @@ void with_edge(bool edge, Fn&& fn) {
     if (edge) fn(std::true_type{}); else fn(std::false_type{});
 }
 
+// LDS that a launch asks for beyond its tile, to hold five workgroups of a
+// compute unit instead of seven, where bf16 rows end inside a tile: their codes
+// leave as partial lines, which more tiles in flight evict before they are whole
+// (cast of 8192 x 4095 43.9 -> 38.7 us, quantise 46.9 -> 41.2; rows of whole
+// tiles and narrower tensors lose by it or do not care).
+template <int DT>
+constexpr unsigned spare_lds(int64_t cols) {
+    return DT == FP8_DT_BF16 && cols > kCastCols && cols % kCastCols != 0 ? 16u << 10 : 0u;
+}
+
 // fp32 casts of whole tiles with all of a lane's loads in flight at once (90
 // registers), or interleaved with the conversions (about 60).  All at once
 // where few tiles leave the latency open (2048 x 4096: 9.3 us against 10.1) and
@@ -641,7 +737,8 @@ void launch_cast_t(const void* x, int64_t rows, int64_t cols, int64_t ldx, const
         return;
     }
     with_edge(edge, [&](auto E) {
-        hipLaunchKernelGGL((cast_kernel<DT, FMT, decltype(E)::value, true>), dim3((unsigned)ntiles), dim3(kCastThreads), 0, s,
+        hipLaunchKernelGGL((cast_kernel<DT, FMT, decltype(E)::value, true>), dim3((unsigned)ntiles), dim3(kCastThreads),
+                           spare_lds<DT>(cols), s,
                            x, rows, cols, ldx, bias, q, ldq, qT, ldqT, tiles_c);
     });
 }
@@ -677,7 +774,8 @@ void launch_quantise_t(const void* x, int64_t rows, int64_t cols, int64_t ldx, i
     with_edge(has_edge(rows, cols), [&](auto E) {
         constexpr bool kE = decltype(E)::value;
         if (bias_pred)
-            hipLaunchKernelGGL((quant_pass1_kernel<DT, FMT, true, kE>), dim3((unsigned)ntiles), dim3(kCastThreads), 0, s,
+            hipLaunchKernelGGL((quant_pass1_kernel<DT, FMT, true, kE>), dim3((unsigned)ntiles), dim3(kCastThreads),
+                               spare_lds<DT>(cols), s,
                                x, rows, cols, ldx, bias_pred, used, parts, q, ldq, qT, ldqT, tiles_c);
         else
             hipLaunchKernelGGL((quant_pass1_kernel<DT, FMT, false, kE>), dim3((unsigned)ntiles), dim3(kCastThreads), 0, s,
@@ -756,7 +854,7 @@ void launch_quantise_delayed_t(const void* x, int64_t rows, int64_t cols, int64_
     if (ntiles > 0) {
         with_edge(has_edge(rows, cols), [&](auto E) {
             hipLaunchKernelGGL((quant_pass1_kernel<DT, FMT, true, decltype(E)::value>), dim3((unsigned)ntiles),
-                               dim3(kCastThreads), 0, s, x, rows, cols, ldx, bias, used, parts, q, ldq, qT, ldqT, tiles_c);
+                               dim3(kCastThreads), spare_lds<DT>(cols), s, x, rows, cols, ldx, bias, used, parts, q, ldq, qT, ldqT, tiles_c);
         });
     }
     hipLaunchKernelGGL((quant_delayed_finish_kernel<DT, FMT>), dim3(1), dim3(kCastThreads), 0, s, parts, (int)ntiles,

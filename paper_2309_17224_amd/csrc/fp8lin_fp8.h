@@ -254,24 +254,6 @@ __device__ __forceinline__ uint32_t f32_key(uint32_t u) {  // fp32 pattern -> Na
     return (u >> 16) | ((u & 0xFFFFu) ? 1u : 0u);
 }
 
-template <int DT, int FMT>
-__device__ __forceinline__ uint32_t cast1(const void* x, int64_t idx, int b) {
-    uint32_t key;
-    float f;
-    if (DT == FP8_DT_BF16) {
-        key = ((const uint16_t*)x)[idx];
-        f = __uint_as_float(key << 16);
-    } else {
-        const uint32_t u = ((const uint32_t*)x)[idx];
-        key = f32_key(u);
-        f = __uint_as_float(u);
-    }
-    const float y[4] = {scaled<FMT>(f, b), 0.0f, 0.0f, 0.0f};
-    uint32_t c = cast4<FMT>(y) & 0xFFu;
-    if ((key & 0x7FFFu) > 0x7F80u) c = nan_code<FMT>(key);
-    return c;
-}
-
 // Vector accesses of global memory at any byte address (gfx950 takes them
 // unaligned; an aligned address costs what it did).
 typedef unsigned int u32x2_any __attribute__((ext_vector_type(2), aligned(1)));

@@ -20,7 +20,8 @@ from parity_util import i32, np_bits, u32
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(1, 1), (1, 5), (1, 9), (1, 129), (1, 40001), (3, 7), (5, 128), (127, 129), (128, 120), (129, 127), (136, 8), (45, 300), (301, 264), (255, 1001),
-          (20, 4096), (21, 4096), (4099, 8), (9103, 9), (1025, 129), (1001, 1000), (384, 256)]
+          (20, 4096), (21, 4096), (4099, 8), (9103, 9), (1025, 129), (1001, 1000), (384, 256),
+          (2, 3), (4, 2), (2, 4096), (9, 260), (1000, 1), (300, 3), (1025, 4), (129, 7), (30001, 6)]
 
 
 def view_of(x, strided):
@@ -142,3 +143,28 @@ def test_scale_bias_finds_the_amax_anywhere(gpu, n, dtype):
             x[off + at] = -3.0
             _, a, _ = F.fp8_scale_bias(x[off:off + n], F.E4M3)
             assert u32(a) == 0x40400000, (off, at)
+
+
+@pytest.mark.parametrize("cols", [1, 2, 3, 4, 5, 6, 7])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
+@pytest.mark.parametrize("fmt", [F.E4M3, F.E5_A])
+def test_special_values_in_narrow_rows(orc, gpu, cols, dtype, fmt):
+    """Rows of fewer than eight columns read eight elements, those of other
+    rows among them: infinities and NaN beside every row, in the last rows
+    (whose vectors end at the tensor's end) and past the tensor."""
+    rows = 139
+    for strided in (False, True):
+        x = wl.small(rows, cols, 1.0, cols).to(dtype)
+        for r, v in ((0, float("inf")), (1, -0.0), (60, float("nan")), (rows - 1, -float("inf")), (rows - 2, float("nan")),
+                     (rows - 3, 9.0), (rows - 7, -float("nan"))):
+            x[r, (r * 5) % cols] = v
+        xb = np_bits(x)
+        ob, oa, ofl = orc.scale_bias(xb, fmt, 1)
+        oq, oqT = orc.cast(xb, fmt, 5, transpose=True)
+        xd = view_of(x, strided)
+        b5 = torch.tensor([5], dtype=torch.int32, device=gpu)
+        q, qT = F.fp8_cast(xd, fmt, b5, want_qT=True)
+        _, _, b, a, fl = F.fp8_quantise(xd, fmt, 1)
+        torch.cuda.synchronize()
+        assert (i32(b), u32(a), u32(fl)) == (ob, oa, ofl)
+        assert np.array_equal(q.cpu().numpy(), oq) and np.array_equal(qT.cpu().numpy(), oqT)
