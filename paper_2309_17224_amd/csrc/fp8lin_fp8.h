@@ -256,6 +256,7 @@ __device__ __forceinline__ uint32_t f32_key(uint32_t u) {  // fp32 pattern -> Na
 
 // Vector accesses of global memory at any byte address (gfx950 takes them
 // unaligned; an aligned address costs what it did).
+typedef unsigned int u32_any __attribute__((aligned(1)));
 typedef unsigned int u32x2_any __attribute__((ext_vector_type(2), aligned(1)));
 typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
 

@@ -146,3 +146,15 @@ def test_forced_rejects(gpu):
     assert R.forced(3, (0, 0), *args) == F.EINVAL              # no such kernel
     odd = t[:, :100].contiguous()
     assert R.forced(R.MAIN, (0, 0), odd, F.E4M3, z, odd, F.E4M3, z, out) == F.EINVAL  # K not a multiple of 128
+
+
+@pytest.mark.parametrize("K", [*range(1, 16), 48, 112, 240])
+def test_contraction_of_few_or_whole_loads(orc, gpu, K):
+    """K < 16: a row's bytes come in one to three overlapping loads; K a
+    multiple of 16: in whole ones, none past the last."""
+    M, N = 67, 130
+    ta, pa, tb, pb, prod = operands(orc, gpu, "fwd", M, N, K)
+    assert R.kernel(M, N, K) == R.RAGGED
+    y = F.fp8_linear_fwd(ta, pa, tb, pb, out_dt=F.DT_F32)
+    torch.cuda.synchronize()
+    assert np.array_equal(np_bits(y), np_bits(prod))
