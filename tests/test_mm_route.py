@@ -42,3 +42,13 @@ def test_amax_changes_the_tile_but_not_the_order_of_the_sums():
     # with the tile that is best without an amax: 22, 17.8 and 25 us with an in-launch bias
     for (m, n, k), most in {(256, 768, 768): 150, (64, 3072, 768): 200, (33, 4096, 4096): 256}.items():
         assert R.workgroups(m, n, *R.route(m, n, k, with_amax=True)[1:]) <= most
+
+
+def test_wide_weights_of_short_rows_take_wide_tiles():
+    """One token through a weight of many short rows: rounds of small
+    workgroups cost more than their copies.  us in 32- or 48-column tiles, and
+    in the widest: 9.8 and 6.7, 7.1 and 5.4, 13.3 and 11.2.
+    Long rows keep what they had."""
+    for n, k in ((57344, 128), (22016, 768), (57344, 768)):
+        assert R.workgroups(1, n, *R.route(1, n, k)[1:]) <= 512, (n, k)
+    assert R.route(1, 22016, 4096)[1:] == (1, 3) and R.route(16, 57344, 8192)[1:] == (1, 2)
