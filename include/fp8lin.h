@@ -341,6 +341,12 @@ int32_t fp8_bias_mode(const int32_t *bias, int64_t n, int32_t *ring, int64_t cap
  * K (rows at any byte address) goes through registers, with the same results
  * as zero padding: measured 4096 x 4096 x 4032 in 89 us and 4096 x 4096 x 1531
  * (grad-weight, fp32) in 57 us, against 63 and 32 us at K = 4096 and 1536.
+ * Order of the sums: a call gives the same bits every time, and the same with
+ * and without y_amax_bits or a fused bias or quantise.  The number of partial
+ * sums over k depends on M, N and K (outputs too small to fill the chip take
+ * small tiles whose waves split k), so the bits of one row of such an output
+ * can differ, within the rounding of the sums, between calls of different M:
+ * a prompt in chunks agrees with the whole one to rounding, not bit for bit.
  * The same rules hold for every matmul entry point below.
  */
 int32_t fp8_linear_fwd(const uint8_t *x8, const int32_t *bx, const uint8_t *w8t, const int32_t *bw,

@@ -15,9 +15,9 @@
 //  * KC = 512 (up to 96 rows): wave w multiplies the whole tile over the 128
 //    bytes of k at 128 w of each stage.  KC = 256 (up to 192 rows): waves w
 //    and w + 2 share a 128-byte slice, each half of the tile's columns.  No
-//    fragment is read from LDS twice.  KC = 128 (256 rows, for 128 to 512 rows
-//    of A): the waves take quarters of the tile, and k is not split
-//    (512 x 8192 x 8192: 67 us in 256-row tiles, 61 in 8 x 4, 48 in 8 x 8).
+//    fragment is read from LDS twice.  KC = 128 (256 rows): the waves take
+//    quarters of the tile, and k is not split (512 x 8192 x 8192: 67 us in
+//    256-row tiles, 61 in 8 x 4, 48 in 8 x 8).
 //  * The partial sums are added through LDS in a fixed order, so the
 //    result does not depend on timing.
 //  * 16-byte chunk c of LDS row r is stored at chunk c ^ (r % 16): the lanes
@@ -212,7 +212,8 @@ void launch_one(const MmArgs& a, hipStream_t s) {
 }
 
 // Tile shapes (16-row blocks of A and of B) the kernel is built for: those the
-// rule below chooses somewhere for 1 to 2048 rows and weights of 128 to 57344.
+// rule below chooses somewhere for 1 to 2048 rows and weights of 128 to 57344
+// ((1, 4), (4, 2) and (8, 4) only for calls that take the amax).
 #define FP8LIN_STREAM_TILES(X)                                                                             \
     X(1, 1) X(1, 2) X(1, 3) X(1, 4) X(1, 5) X(1, 6) X(1, 8) X(2, 1) X(2, 2) X(2, 3) X(2, 4) X(2, 6) X(2, 8)  \
     X(3, 1) X(3, 2) X(3, 3) X(3, 4) X(3, 6) X(3, 8) X(4, 2) X(4, 4) X(4, 6) X(4, 8) X(5, 2) X(5, 4) X(5, 6) \

@@ -410,8 +410,8 @@ class WorkloadStep:
         for l in lin:
             xq, wq, o = self.q[l.x], self.q[l.w], self.out[l.name]
             flop = 2 * l.M * l.N * l.K
-            # M <= 32 runs the weight-streaming kernel: its work is counted in
-            # bytes (weight + activations + bf16 output), it is HBM-bound
+            # M <= 32 (a decode step): bound by the weight's bytes, so its work is
+            # counted in bytes (weight + activations + bf16 output)
             kind, work = "gemm_fwd", flop
             if l.M <= 32:
                 kind, work = "gemm_decode", l.N * l.K + l.M * l.K + 2 * l.M * l.N
