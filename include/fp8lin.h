@@ -370,7 +370,7 @@ int32_t fp8_linear_bwd_dx(const uint8_t *dy8, const int32_t *bg, const uint8_t *
  * y / dx, bias, amax and flags as the matmul with y_amax_bits followed by
  * fp8_bias_from_amax, without the separate zeroing launch, and without the
  * bias launch (the last workgroup of the matmul to finish computes the bias)
- * but for outputs of more than 64 small tiles, whose workgroups all finish at
+ * but for outputs of more than 256 small tiles, whose workgroups all finish at
  * once: there one thread computes it in a launch after the matmul.
  * y / dx:  out, as fp8_linear_fwd / fp8_linear_bwd_dx (bf16 or fp32).
  * *_fmt, margin: format and margin of the bias (as fp8_scale_bias).

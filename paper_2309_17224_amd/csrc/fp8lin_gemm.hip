@@ -471,10 +471,13 @@ __global__ void bias_finish_kernel(uint32_t* amax_out, BiasOut bo) {
 // Most workgroups of a small-tile launch that take the bias in the launch
 // itself.  Small tiles finish together, and the device performs one atomic on
 // a word after another: 9 ns for a fold alone, 18 ns for a fold and a count,
-// which a launch of bias_finish_kernel (2 us) saves from about 64 workgroups
-// on (768 x 768 x 768, 256 workgroups: 12.4 us, 10.5 with the launch, 5.9
-// without a bias).  The 256 x 256 tiles are few or finish apart.
-constexpr int64_t kFoldInLaunch = 64;
+// which a launch of bias_finish_kernel would save from 64 workgroups on (in the
+// launch and after it: 128 workgroups 8.4 and 8.0 us, 192 10.8 and 9.1, 256
+// 12.0 and 10.0).  But the host takes 3.7 us to launch it, which is what bounds
+// small layers called one by one (training step of 1024 x 768 x 768: 73 us, 80
+// with two such launches), so only outputs of more tiles than compute units
+// take it.  The 256 x 256 tiles are few or finish apart.
+constexpr int64_t kFoldInLaunch = 256;
 
 // Columns of 256-wide tiles taken in whole rounds of kRound workgroups, and
 // the rest in one round of narrower tiles: with all 256-wide, a last partial

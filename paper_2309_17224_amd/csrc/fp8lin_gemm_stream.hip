@@ -280,7 +280,7 @@ static double stream_us(int64_t M, int64_t N, int64_t K) {
 
 // Every workgroup's fold of its maximum into one word waits for those before
 // it, part of which hides behind workgroups that are still multiplying (us).
-constexpr double kFoldUs = 0.005;
+constexpr double kFoldUs = 0.009;
 
 // The tile with the smallest estimate.  With an epilogue amax, of the tiles
 // that sum in the same order (the same KC), so that an output's bits do not

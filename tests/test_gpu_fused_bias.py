@@ -94,9 +94,9 @@ def test_dx_bias_matches_unfused(gpu, shape, fmt):
 
 
 # The plain product and the one with a bias take different tiles; the bias comes
-# from the launch itself (few workgroups) or from one after it (more than 64).
+# from the launch itself or from one after it (more than 256 workgroups).
 @pytest.mark.parametrize("shape", [(33, 768, 768), (256, 768, 768), (100, 2304, 768), (1024, 768, 768), (301, 4096, 4096),
-                                   (130, 200, 100), (700, 1000, 100)], ids=str)
+                                   (130, 200, 100), (700, 1000, 100), (2049, 5000, 100), (4000, 4100, 100)], ids=str)
 def test_output_bits_do_not_depend_on_the_bias(gpu, shape):
     M, N, K = shape
     x8, bx, w8t, bw = operands(gpu, M, N, K, 3 * M + N)
